@@ -5,8 +5,10 @@ Usage: ``python -m paper_0808_3510_amd.build`` (or ``build()`` from Python).
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -14,13 +16,36 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpatnufft.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["plan.cpp", "capi.cpp", "kernels.hip"]
+SOURCES = ["plan.cpp", "capi.cpp", "general.hip", "kernels.hip"]
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions are kept out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+
+
+def _compile(flags: list[str], lib: str, verbose: bool):
+    """The sources side by side (each takes a minute or two), then one link."""
+    tmp = tempfile.mkdtemp(prefix="build_", dir=HERE)
+    try:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        runs = [subprocess.Popen([HIPCC, *flags, "-c", "-I" + os.path.join(ROOT, "include"), os.path.join(CSRC, s),
+                                  "-o", o], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+                for s, o in zip(SOURCES, objs)]
+        outs = [r.communicate()[0] for r in runs]
+        failed = any(r.returncode != 0 for r in runs)
+        if not failed:
+            res = subprocess.run([HIPCC, *flags, "-shared", *objs, "-o", lib + ".tmp"], capture_output=True, text=True)
+            outs.append(res.stdout + res.stderr)
+            failed = res.returncode != 0
+        if verbose or failed:
+            sys.stderr.write("".join(outs))
+        if failed:
+            raise RuntimeError("hipcc failed building " + os.path.basename(lib))
+        os.replace(lib + ".tmp", lib)
+    finally:
+        shutil.rmtree(tmp, ignore_errors=True)
 
 
 SAN_LIB = os.path.join(ROOT, "_build", "libpatnufft_hostsan.so")
@@ -34,18 +59,11 @@ def build_host_sanitized(verbose: bool = False) -> str:
     os.makedirs(os.path.dirname(SAN_LIB), exist_ok=True)
     # (device code at -O1 for a quick build; the sanitizers apply to the host
     # side only, each -fsanitize= behind -Xarch_host)
-    cmd = [HIPCC, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
-           "-Xarch_host", "-fno-sanitize-recover=all", "-Xarch_host", "-fno-omit-frame-pointer",
-           "-Xarch_host", "-shared-libsan", "-I" + os.path.join(ROOT, "include"),
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", SAN_LIB]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building the sanitized host library")
-    if verbose:
-        sys.stderr.write(res.stderr)
+    _compile(["--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-fPIC",
+              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+              "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
+              "-Xarch_host", "-fno-sanitize-recover=all", "-Xarch_host", "-fno-omit-frame-pointer",
+              "-Xarch_host", "-shared-libsan"], SAN_LIB, verbose)
     return SAN_LIB
 
 
@@ -59,15 +77,7 @@ def asan_runtime() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    cmd = [HIPCC, *FLAGS, "-I" + os.path.join(ROOT, "include"),
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB + ".tmp"]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libpatnufft.so")
-    if verbose:
-        sys.stderr.write(res.stderr)
-    os.replace(LIB + ".tmp", LIB)
+    _compile(FLAGS, LIB, verbose)
     return LIB
 
 

@@ -1,0 +1,1317 @@
+// General-length kernels: the transverse passes and the fused line stages for
+// every length whose factors group into two or three radices up to 23, with
+// run-time sizes, for one instance or a whole batch in one launch per stage.
+//
+//   k_gtr_x1    DFT over the first detector axis, real input, half spectrum
+//   k_gtr_x2    DFT over the second detector axis (either direction, in place)
+//   k_gtr_c2r   inverse DFT over the first axis from the half spectrum
+//   k_gline2    a2 + a3 + inverse depth DFT (R, A^T)
+//   k_gline1    depth DFT + spreading + transposed a2 (R^T, A)
+//
+// Every FFT is a GFft (pat_internal.h): each stage loads one butterfly's
+// points into registers, transforms them with a fully unrolled R-point DFT
+// whose roots are compile-time constants, and writes them back; the first
+// stage of a pass reads from memory and the last one writes to memory, so a
+// two-stage length crosses LDS once.  The last stage has no twiddles, and the
+// plan puts the large primes there.
+#include "general.h"
+
+namespace pat {
+
+// Descriptors are read through the constant address space: their fields then
+// come by scalar loads, once, whatever the kernel stores in between (through a
+// plain pointer they were vector loads, repeated after every barrier: the
+// fused type-2 kernel took 79 instead of XX us at 152 x 136 x 368).
+using CInst = const __attribute__((address_space(4))) Inst;
+using CFft = const __attribute__((address_space(4))) GFft;
+
+__device__ __forceinline__ int fdiv(int n, uint32_t m) { return m ? (int)__umulhi((unsigned)n, m) : n; }
+
+// ---------------------------------------------------------------------------
+// R-point DFTs in registers, natural order in and out.
+
+template <typename T, int R>
+__device__ __forceinline__ void dft_reg(cx<T>* v);
+
+// odd prime, by the symmetric form of bfly_prime with every root a constant
+template <typename T, int R>
+__device__ __forceinline__ void dft_prime(cx<T>* v) {
+  constexpr int H = (R - 1) / 2;
+  cx<T> av[H], bv[H];
+  const cx<T> x0 = v[0];
+  cx<T> s = x0;
+#pragma unroll
+  for (int r = 1; r <= H; ++r) {
+    av[r - 1] = cadd(v[r], v[R - r]);
+    bv[r - 1] = csub(v[r], v[R - r]);
+    s = cadd(s, av[r - 1]);
+  }
+  v[0] = s;
+#pragma unroll
+  for (int d = 1; d <= H; ++d) {
+    cx<T> A = x0, B = mk(T(0), T(0));
+#pragma unroll
+    for (int r = 1; r <= H; ++r) {
+      const T c = T(Roots<R>::t.c[(r * d) % R]), sn = T(Roots<R>::t.s[(r * d) % R]);
+      A.x += av[r - 1].x * c;
+      A.y += av[r - 1].y * c;
+      B.x += bv[r - 1].x * sn;
+      B.y += bv[r - 1].y * sn;
+    }
+    v[d] = mk(A.x + B.y, A.y - B.x);
+    v[R - d] = mk(A.x - B.y, A.y + B.x);
+  }
+}
+
+// R = A B with coprime factors (prime-factor map): input n = B n1 + A n2,
+// output k with k = k1 mod A, k = k2 mod B; no twiddles
+constexpr int crt(int A, int B, int k1, int k2) {
+  for (int k = 0; k < A * B; ++k)
+    if (k % A == k1 && k % B == k2) return k;
+  return 0;
+}
+template <typename T, int A, int B>
+__device__ __forceinline__ void dft_pfa(cx<T>* v) {
+  cx<T> t[A][B];
+#pragma unroll
+  for (int i = 0; i < A; ++i) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) t[i][j] = v[(B * i + A * j) % (A * B)];
+    dft_reg<T, B>(t[i]);
+  }
+#pragma unroll
+  for (int j = 0; j < B; ++j) {
+    cx<T> u[A];
+#pragma unroll
+    for (int i = 0; i < A; ++i) u[i] = t[i][j];
+    dft_reg<T, A>(u);
+#pragma unroll
+    for (int i = 0; i < A; ++i) v[crt(A, B, i, j)] = u[i];
+  }
+}
+
+// 9 = 3 x 3 with the roots of 9 between the two steps
+template <typename T>
+__device__ __forceinline__ void dft_9(cx<T>* v) {
+  cx<T> t[3][3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) t[i][j] = v[3 * j + i];
+    dft_reg<T, 3>(t[i]);
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    cx<T> u[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const T c = T(Roots<9>::t.c[i * j]), s = T(Roots<9>::t.s[i * j]);
+      u[i] = mk(t[i][j].x * c + t[i][j].y * s, t[i][j].y * c - t[i][j].x * s);
+    }
+    dft_reg<T, 3>(u);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[3 * i + j] = u[i];
+  }
+}
+
+template <typename T, int R>
+__device__ __forceinline__ void dft_reg(cx<T>* v) {
+  if constexpr (R == 1) {
+  } else if constexpr (R == 2 || R == 4 || R == 8 || R == 16) dft_pow2<T, R>(v);
+  else if constexpr (R == 9) dft_9<T>(v);
+  else if constexpr (R == 6) dft_pfa<T, 2, 3>(v);
+  else if constexpr (R == 10) dft_pfa<T, 2, 5>(v);
+  else if constexpr (R == 12) dft_pfa<T, 4, 3>(v);
+  else if constexpr (R == 14) dft_pfa<T, 2, 7>(v);
+  else if constexpr (R == 15) dft_pfa<T, 3, 5>(v);
+  else if constexpr (R == 18) dft_pfa<T, 2, 9>(v);
+  else if constexpr (R == 20) dft_pfa<T, 4, 5>(v);
+  else if constexpr (R == 21) dft_pfa<T, 3, 7>(v);
+  else if constexpr (R == 22) dft_pfa<T, 2, 11>(v);
+  else dft_prime<T, R>(v);
+}
+
+// The R outputs of a butterfly handed to emit(k, X_k): the larger primes one
+// output pair at a time (their R outputs beside the R combined inputs would
+// not fit in registers), the others after the whole transform.
+template <typename T, int R, typename Emit>
+__device__ __forceinline__ void dft_emit(cx<T>* v, Emit emit) {
+  if constexpr (R == 13 || R == 17 || R == 19 || R == 23) {
+    constexpr int H = (R - 1) / 2;
+    cx<T> s = v[0];
+#pragma unroll
+    for (int r = 1; r <= H; ++r) {
+      const cx<T> p = cadd(v[r], v[R - r]);
+      v[R - r] = csub(v[r], v[R - r]);
+      v[r] = p;
+      s = cadd(s, p);
+    }
+    emit(0, s);
+#pragma unroll
+    for (int d = 1; d <= H; ++d) {
+      cx<T> A = v[0], B = mk(T(0), T(0));
+#pragma unroll
+      for (int r = 1; r <= H; ++r) {
+        const T c = T(Roots<R>::t.c[(r * d) % R]), sn = T(Roots<R>::t.s[(r * d) % R]);
+        A.x += v[r].x * c;
+        A.y += v[r].y * c;
+        B.x += v[R - r].x * sn;
+        B.y += v[R - r].y * sn;
+      }
+      emit(d, mk(A.x + B.y, A.y - B.x));
+      emit(R - d, mk(A.x - B.y, A.y + B.x));
+    }
+  } else {
+    dft_reg<T, R>(v);
+#pragma unroll
+    for (int d = 0; d < R; ++d) emit(d, v[d]);
+  }
+}
+
+// f.operator()<R>() for the run-time radix r of a twiddled stage (the set
+// plan_general takes r0 and r1 from) and of a last stage
+template <int R>
+struct RadixTag {
+  static constexpr int v = R;
+};
+#define PAT_CASE(R) \
+  case R: f(RadixTag<R>{}); break;
+template <typename F>
+__device__ __forceinline__ void with_tw_radix(int r, F f) {
+  switch (r) {
+    PAT_CASE(1) PAT_CASE(2) PAT_CASE(3) PAT_CASE(4) PAT_CASE(5) PAT_CASE(6) PAT_CASE(7) PAT_CASE(8) PAT_CASE(9)
+    PAT_CASE(10) PAT_CASE(11) PAT_CASE(12) PAT_CASE(13) PAT_CASE(16)
+    default: break;
+  }
+}
+template <typename F>
+__device__ __forceinline__ void with_last_radix(int r, F f) {
+  switch (r) {
+    PAT_CASE(2) PAT_CASE(3) PAT_CASE(4) PAT_CASE(5) PAT_CASE(6) PAT_CASE(7) PAT_CASE(8) PAT_CASE(9) PAT_CASE(10)
+    PAT_CASE(11) PAT_CASE(12) PAT_CASE(13) PAT_CASE(14) PAT_CASE(15) PAT_CASE(16) PAT_CASE(17) PAT_CASE(18)
+    PAT_CASE(19) PAT_CASE(20) PAT_CASE(21) PAT_CASE(22) PAT_CASE(23)
+    default: break;
+  }
+}
+
+// element at a 32-bit byte offset from a workgroup-uniform base
+template <typename V>
+__device__ __forceinline__ V* at_off(V* base, uint32_t bytes) {
+  using C = std::conditional_t<std::is_const_v<V>, const char, char>;
+  return reinterpret_cast<V*>(reinterpret_cast<C*>(base) + bytes);
+}
+
+template <typename T, bool NT>
+__device__ __forceinline__ cx<T> ld_cx(const cx<T>* p) {
+  if constexpr (NT && sizeof(T) == 4) {
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const v2f v = __builtin_nontemporal_load(reinterpret_cast<const v2f*>(p));
+    return mk(v.x, v.y);
+  } else {
+    return *p;
+  }
+}
+template <typename T, bool NT>
+__device__ __forceinline__ void st_cx(cx<T>* p, cx<T> v) {
+  if constexpr (NT && sizeof(T) == 4) {
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const v2f u = {v.x, v.y};
+    __builtin_nontemporal_store(u, reinterpret_cast<v2f*>(p));
+  } else {
+    *p = v;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Transverse passes: tiles of tb columns (a power of two; the contiguous t or
+// z axis) by the full transform length; lanes run along the columns.
+
+// Twiddled first stage: the rows come from load(row), and go to buf.
+template <typename T, typename Load>
+__device__ __forceinline__ void gtr_first(CFft& g, cx<T>* buf, const cx<T>* tw, int ltb, Load load) {
+  const int tb = 1 << ltb, total = g.sub0 << ltb;
+  with_tw_radix(g.r0, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < total; id += kBlock) {
+      const int col = id & (tb - 1), j = id >> ltb;
+      cx<T> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = load(j + r * g.sub0, col);
+      // point d2 rl + e of sub-transform r: row r bs + d2 rlp + e
+      cx<T>* p = buf + ((j + fdiv(j, g.m_rl) * (g.rlp - g.rl)) << ltb) + col;
+      const int st = g.bs << ltb;
+      dft_emit<T, R>(v, [&](int d, cx<T> x) { p[d * st] = d ? cmul(x, tw[j * d]) : x; });
+    }
+  });
+  __syncthreads();
+}
+
+// Twiddled middle stage, in place (three-stage lengths).
+template <typename T>
+__device__ __forceinline__ void gtr_mid(CFft& g, cx<T>* buf, const cx<T>* tw, int ltb) {
+  if (g.r1 == 1) return;
+  const int tb = 1 << ltb, total = (g.r0 * g.rl) << ltb;
+  with_tw_radix(g.r1, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < total; id += kBlock) {
+      const int col = id & (tb - 1), bf = id >> ltb;
+      const int blk = fdiv(bf, g.m_rl), j = bf - blk * g.rl;
+      cx<T>* p = buf + ((blk * g.bs + j) << ltb) + col;
+      const int st = g.rlp << ltb;
+      cx<T> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = p[r * st];
+      dft_emit<T, R>(v, [&](int d, cx<T> x) { p[d * st] = d ? cmul(x, tw[j * d * g.r0]) : x; });
+    }
+  });
+  __syncthreads();
+}
+
+// Last stage: store(k, col, X_k) receives every output.
+template <typename T, typename Store>
+__device__ __forceinline__ void gtr_last(CFft& g, const cx<T>* buf, int ltb, Store store) {
+  const int tb = 1 << ltb, total = g.nbl << ltb;
+  with_last_radix(g.rl, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < total; id += kBlock) {
+      const int col = id & (tb - 1), bf = id >> ltb;
+      const int d1 = fdiv(bf, g.m_r1), d2 = bf - d1 * g.r1;
+      const cx<T>* p = buf + ((d1 * g.bs + d2 * g.rlp) << ltb) + col;
+      cx<T> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = p[r << ltb];
+      const int k0 = d1 + g.r0 * d2;
+      dft_emit<T, R>(v, [&](int r, cx<T> x) { store(k0 + r * g.nbl, col, x); });
+    }
+  });
+}
+
+template <typename T>
+constexpr int gtr_waves() { return sizeof(T) == 4 ? 4 : 2; }
+
+// Item of slot i: workgroups go to the eight XCDs in turn, so slot i runs on
+// XCD i mod 8; each XCD gets one contiguous run of items, whose neighbours (tiles
+// that share cache lines where a row is no multiple of a line) then meet in
+// its L2.
+__device__ __forceinline__ int xcd_item(int i, int total) {
+  const int q = total >> 3, r = total & 7, x = i & 7;
+  return x * q + min(x, r) + (i >> 3);
+}
+
+// Loop over the items of a persistent grid: item, its instance I and its index
+// li within the instance; `fresh` when the instance differs from the last.
+#define PAT_G_ITEMS(a)                                                             \
+  int cur_ = -1;                                                                   \
+  for (int it_ = blockIdx.x; it_ < (a).total; it_ += gridDim.x) {                  \
+    const int item = xcd_item(it_, (a).total);                                     \
+    const int inst = __builtin_amdgcn_readfirstlane(find_inst(a, item));           \
+    const bool fresh = inst != cur_;                                               \
+    cur_ = inst;                                                                   \
+    CInst& I = *(CInst*)(a).inst[inst];                                              \
+    const int li = item - (a).off[inst];
+
+template <typename T>
+__device__ __forceinline__ void g_roots(cx<T>* dst, CInst& I, CFft& g) {
+  const cx<T>* src = static_cast<const cx<T>*>(I.tw) + g.tw;
+  for (int e = threadIdx.x; e < g.L; e += kBlock) dst[e] = src[e];
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x1(StageArgs a) {
+  PAT_G_ITEMS(a)
+  CFft& g = I.g1;
+  cx<T>* tw = reinterpret_cast<cx<T>*>(pat_smem);
+  cx<T>* buf = tw + g.L;
+  __syncthreads();
+  if (fresh) {
+    g_roots(tw, I, g);
+    __syncthreads();
+  }
+  const int len = a.len_nz ? I.nz : I.nt;  // even
+  const int tb = I.gtb1, ltb = __builtin_ctz((unsigned)tb);
+  const int ntile = (len + 2 * tb - 1) / (2 * tb);
+  const int x2 = li / ntile;
+  const int t0 = (li - x2 * ntile) * 2 * tb;
+  const size_t base = (size_t)x2 * len + t0;
+  const cx<T>* in = reinterpret_cast<const cx<T>*>(static_cast<const T*>(a.in[inst]) + base);
+  cx<T>* out = static_cast<cx<T>*>(a.out[inst]) + base;
+  const uint32_t row = (uint32_t)(I.n2 * len) * (uint32_t)sizeof(T);  // bytes of a real row
+  const int w = (len - t0) >> 1;  // columns of this tile
+  // complex column b holds the samples t0 + 2b (real part) and t0 + 2b + 1
+  gtr_first<T>(g, buf, tw, ltb, [&](int x, int b) {
+    return b < w ? ld_cx<T, true>(at_off(in, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)))
+                 : mk(T(0), T(0));
+  });
+  gtr_mid<T>(g, buf, tw, ltb);
+  // in place: output r of a butterfly goes to the row its input r came from
+  with_last_radix(g.rl, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < (g.nbl << ltb); id += kBlock) {
+      const int col = id & (tb - 1), bf = id >> ltb;
+      const int d1 = fdiv(bf, g.m_r1), d2 = bf - d1 * g.r1;
+      cx<T>* p = buf + ((d1 * g.bs + d2 * g.rlp) << ltb) + col;
+      cx<T> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = p[r << ltb];
+      dft_emit<T, R>(v, [&](int r, cx<T> x) { p[r << ltb] = x; });
+    }
+  });
+  __syncthreads();
+  // The transforms of the two samples: bin k of the columns' transform Z and
+  // the conjugate of bin L - k give pa and pb.  A thread walks the outputs
+  // k = n + d nbl of one butterfly n and the outputs of its mirror butterfly
+  // (their LDS rows differ by one per step).
+  const int nb = g.nbl << ltb, half = g.L / 2;
+  const int nq = nb < kBlock ? kBlock / nb : 1;  // threads per butterfly
+  for (int id = threadIdx.x; id < nb * nq; id += kBlock) {
+    const int b = id & (tb - 1), q = fdiv(id >> ltb, g.m_nbl), n = (id >> ltb) - q * g.nbl;
+    if (b >= w) continue;
+    const int nm = n ? g.nbl - n : 0;
+    const int e2 = fdiv(n, g.m_r0), f2 = fdiv(nm, g.m_r0);
+    const cx<T>* own = buf + (((n - e2 * g.r0) * g.bs + e2 * g.rlp) << ltb) + b;
+    const cx<T>* mir = buf + (((nm - f2 * g.r0) * g.bs + f2 * g.rlp) << ltb) + b;
+    const uint32_t ob = (uint32_t)b * (uint32_t)(2 * sizeof(cx<T>));
+    for (int d = q; n + d * g.nbl <= half; d += nq) {
+      const int k = n + d * g.nbl;
+      const int dm = n ? g.rl - 1 - d : d ? g.rl - d : 0;
+      const cx<T> z = own[d << ltb], zn = cconj(mir[dm << ltb]);
+      const T h = T(0.5);
+      const cx<T> pa = cscl(cadd(z, zn), h);
+      const cx<T> df = csub(z, zn);
+      const cx<T> pb = mk(h * df.y, -h * df.x);
+      st_pair(at_off(out, (uint32_t)k * (2 * row) + ob), pa, pb);
+    }
+  }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x2(StageArgs a) {
+  PAT_G_ITEMS(a)
+  CFft& g = I.g2;
+  cx<T>* tw = reinterpret_cast<cx<T>*>(pat_smem);
+  cx<T>* buf = tw + g.L;
+  __syncthreads();
+  if (fresh) {
+    g_roots(tw, I, g);
+    __syncthreads();
+  }
+  const int len = a.len_nz ? I.nz : I.nt;
+  const int tb = I.gtb2, ltb = __builtin_ctz((unsigned)tb);
+  const int ntile = (len + tb - 1) / tb;
+  const int k1 = li / ntile;
+  const int t0 = (li - k1 * ntile) * tb;
+  cx<T>* io = static_cast<cx<T>*>(a.out[inst]) + (size_t)k1 * I.n2 * len + t0;
+  const uint32_t row = (uint32_t)len * (uint32_t)sizeof(cx<T>);
+  const int w = len - t0;
+  const T sg = a.mode != 0 ? T(-1) : T(1);  // the inverse as conj(FFT(conj(.)))
+  gtr_first<T>(g, buf, tw, ltb, [&](int x, int b) {
+    const cx<T> v = b < w ? *at_off(io, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)) : mk(T(0), T(0));
+    return mk(v.x, sg * v.y);
+  });
+  gtr_mid<T>(g, buf, tw, ltb);
+  gtr_last<T>(g, buf, ltb, [&](int k, int b, cx<T> v) {
+    if (b < w) *at_off(io, (uint32_t)k * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)) = mk(v.x, sg * v.y);
+  });
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_c2r(StageArgs a) {
+  PAT_G_ITEMS(a)
+  CFft& g = I.g1;
+  cx<T>* tw = reinterpret_cast<cx<T>*>(pat_smem);
+  cx<T>* buf = tw + g.L;
+  __syncthreads();
+  if (fresh) {
+    g_roots(tw, I, g);
+    __syncthreads();
+  }
+  const int len = a.len_nz ? I.nz : I.nt;
+  const int tb = I.gtb1, ltb = __builtin_ctz((unsigned)tb);
+  const int ntile = (len + 2 * tb - 1) / (2 * tb);
+  const int x2 = li / ntile;
+  const int t0 = (li - x2 * ntile) * 2 * tb;
+  const size_t base = (size_t)x2 * len + t0;
+  const cx<T>* in = static_cast<const cx<T>*>(a.in[inst]) + base;
+  cx<T>* out = reinterpret_cast<cx<T>*>(static_cast<T*>(a.out[inst]) + base);
+  const uint32_t row = (uint32_t)(I.n2 * len) * (uint32_t)sizeof(T);
+  const int w = (len - t0) >> 1, half = g.L / 2;
+  gtr_first<T>(g, buf, tw, ltb, [&](int k, int b) {
+    // Z = X_a + i X_b of two neighbouring samples, stored conjugated; bins
+    // above n1/2 are the conjugates of their mirror bins, and the imaginary
+    // parts of the bins 0 and n1/2 are dropped (the real part of the inverse)
+    const int src = k <= half ? k : g.L - k;
+    cx<T> xa = mk(T(0), T(0)), xb = mk(T(0), T(0));
+    if (b < w) ld_pair(at_off(in, (uint32_t)src * (2 * row) + (uint32_t)b * (uint32_t)(2 * sizeof(cx<T>))), &xa, &xb);
+    const T sg = k == 0 || k == half ? T(0) : k > half ? T(-1) : T(1);
+    // (multiplied only where a sign is wanted: 0 times an infinite part would
+    // not be 0)
+    const T ya = sg == T(0) ? T(0) : sg * xa.y, yb = sg == T(0) ? T(0) : sg * xb.y;
+    return mk(xa.x - yb, -(ya + xb.x));
+  });
+  gtr_mid<T>(g, buf, tw, ltb);
+  gtr_last<T>(g, buf, ltb, [&](int x, int b, cx<T> v) {
+    if (b < w) st_cx<T, true>(at_off(out, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)), mk(v.x, -v.y));
+  });
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Line stages.  A point of a line pair holds both lines' values side by side
+// (one 16-byte LDS access in float), so that the two lines share index
+// arithmetic, twiddles and, for the mirror lines (k1, +-k2) of a 3D plan, the
+// node windows, phases and weights.  2D plans have no mirror lines: a "pair"
+// is one line there, its second half zero.
+
+template <typename T>
+struct alignas(16) px {
+  cx<T> a, b;
+};
+
+// lines and |K_x|^2 terms of pair P
+struct PairLines {
+  int la, lb;     // line indices (lb = -1: none)
+  bool shared;    // the second line has the first one's nodes (or is absent)
+  double ka, kb;  // nu+^2 = k. + b l^2
+};
+__device__ __forceinline__ PairLines pair_lines(CInst& I, int P) {
+  PairLines q;
+  if (I.n2 == 1) {
+    q.la = P;
+    q.lb = -1;
+    q.shared = true;
+    q.ka = q.kb = I.a1 * (double)P * (double)P;
+    return q;
+  }
+  const int h2 = I.n2 >> 1;
+  const int k1 = fdiv(P, I.m_h2), r = P - k1 * h2;
+  q.la = k1 * I.n2 + r;
+  q.lb = k1 * I.n2 + (r ? I.n2 - r : h2);
+  q.shared = r != 0;
+  const double k1t = I.a1 * (double)k1 * (double)k1;
+  q.ka = k1t + I.a2 * (double)r * (double)r;
+  q.kb = r ? q.ka : k1t + I.a2 * (double)h2 * (double)h2;
+  return q;
+}
+
+// line index of one half of pair P (-1: none)
+__device__ __forceinline__ int pair_line(CInst& I, int P, int half) {
+  if (I.n2 == 1) return half ? -1 : P;
+  const int h2 = I.n2 >> 1;
+  const int k1 = fdiv(P, I.m_h2), r = P - k1 * h2;
+  return k1 * I.n2 + (half ? (r ? I.n2 - r : h2) : r);
+}
+
+// DFT of both halves of R pair points
+template <typename T, int R>
+__device__ __forceinline__ void dft_px(px<T>* v) {
+  cx<T> u[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) u[r] = v[r].a;
+  dft_reg<T, R>(u);
+#pragma unroll
+  for (int r = 0; r < R; ++r) v[r].a = u[r];
+#pragma unroll
+  for (int r = 0; r < R; ++r) u[r] = v[r].b;
+  dft_reg<T, R>(u);
+#pragma unroll
+  for (int r = 0; r < R; ++r) v[r].b = u[r];
+}
+template <typename T>
+__device__ __forceinline__ px<T> pmul(px<T> v, cx<T> w) {
+  v.a = cmul(v.a, w);
+  v.b = cmul(v.b, w);
+  return v;
+}
+
+// v[d] *= w^d, d = 1 .. R-1 (a power of two up to 16), powers by a product
+// tree at most four products deep
+template <typename T, int R>
+__device__ __forceinline__ void twiddle_reg(cx<T>* v, cx<T> w1) {
+  cx<T> w[R > 1 ? R : 2];
+  w[1] = w1;
+#pragma unroll
+  for (int d = 2; d < R; ++d) w[d] = (d & (d - 1)) == 0 ? cmul(w[d / 2], w[d / 2]) : cmul(w[d & (d - 1)], w[d & -d]);
+#pragma unroll
+  for (int d = 1; d < R; ++d) v[d] = cmul(v[d], w[d]);
+}
+template <typename T, int R>
+__device__ __forceinline__ void twiddle_px(px<T>* v, cx<T> w1) {
+  cx<T> w[R > 1 ? R : 2];
+  w[1] = w1;
+#pragma unroll
+  for (int d = 2; d < R; ++d) w[d] = (d & (d - 1)) == 0 ? cmul(w[d / 2], w[d / 2]) : cmul(w[d & (d - 1)], w[d & -d]);
+#pragma unroll
+  for (int d = 1; d < R; ++d) v[d] = pmul(v[d], w[d]);
+}
+
+// One butterfly of R pair points, one half after the other (both at once would
+// not fit in registers for the larger radices): get(r, half) reads the inputs,
+// tw(d, X) applies the twiddle of output d, put(r, half, X) receives them.
+template <typename T, int R, typename Get, typename Tw, typename Put>
+__device__ __forceinline__ void bfly_px(Get get, Tw tw, Put put) {
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    cx<T> v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = get(r, h);
+    dft_emit<T, R>(v, [&](int d, cx<T> x) { put(d, h, d ? tw(d, x) : x); });
+  }
+}
+
+// Stages of the grid FFT (r0 = 8, r1 a power of two, rl one of 8, 10, 12,
+// 14) over the np pairs of an item.  Pair p's points sit at p * rows, point i
+// in row d1 bs + d2 rlp + e (see GFft); NT threads.
+template <typename T>
+__device__ __forceinline__ void grid_mid(CFft& g, px<T>* buf, const cx<T>* tw8, int np) {
+  const int NT = blockDim.x;
+  auto run = [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < np * 8 * g.rl; id += NT) {
+      const int p = fdiv(id, g.m_nb1), q = id - p * (8 * g.rl);
+      const int blk = fdiv(q, g.m_rl), j = q - blk * g.rl;
+      px<T>* s = buf + p * g.rows + blk * g.bs + j;
+      if constexpr (R * sizeof(T) <= 32) {
+        px<T> v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = s[r * g.rlp];
+        dft_px<T, R>(v);
+        twiddle_px<T, R>(v, tw8[j]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) s[r * g.rlp] = v[r];
+      } else {
+        // (both halves at once would not fit in registers)
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+          cx<T>* c = h ? &s->b : &s->a;
+          cx<T> v[R];
+#pragma unroll
+          for (int r = 0; r < R; ++r) v[r] = c[2 * r * g.rlp];
+          dft_reg<T, R>(v);
+          twiddle_reg<T, R>(v, tw8[j]);
+#pragma unroll
+          for (int r = 0; r < R; ++r) c[2 * r * g.rlp] = v[r];
+        }
+      }
+    }
+  };
+  switch (g.r1) {
+    case 2: run(RadixTag<2>{}); break;
+    case 4: run(RadixTag<4>{}); break;
+    case 8: run(RadixTag<8>{}); break;
+    case 16: run(RadixTag<16>{}); break;
+    default: return;
+  }
+  __syncthreads();
+}
+
+// Last grid stage over the natural digits n = d1 + 8 d2 of the butterflies, so
+// that the lanes' outputs k = n + d nbl are neighbours.
+template <typename F>
+__device__ __forceinline__ void with_grid_radix(int r, F f) {
+  switch (r) {
+    PAT_CASE(8) PAT_CASE(10) PAT_CASE(12) PAT_CASE(14)
+    default: break;
+  }
+}
+// In place to natural order (line p at p * rows): at most one butterfly per
+// thread (np nbl <= NT), whose outputs wait in registers until every thread
+// has read its inputs.
+template <typename T>
+__device__ __forceinline__ void grid_last_natural(CFft& g, px<T>* buf, int np) {
+  with_grid_radix(g.rl, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+    const int id = threadIdx.x, lnb = __builtin_ctz((unsigned)g.nbl);
+    const int p = id >> lnb, n = id & (g.nbl - 1);
+    px<T> v[R];
+    if (p < np) {
+      const px<T>* s = buf + p * g.rows + (n & 7) * g.bs + (n >> 3) * g.rlp;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = s[r];
+      dft_px<T, R>(v);
+    }
+    __syncthreads();
+    if (p < np) {
+      px<T>* d = buf + p * g.rows + n;
+#pragma unroll
+      for (int r = 0; r < R; ++r) d[r * g.nbl] = v[r];
+    }
+  });
+}
+// put(p, k, half, X_k) receives the outputs, one half after the other
+template <typename T, typename Put>
+__device__ __forceinline__ void grid_last_put(CFft& g, const px<T>* buf, int np, Put put) {
+  with_grid_radix(g.rl, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+    const int lnb = __builtin_ctz((unsigned)g.nbl);
+#pragma unroll 1
+    for (int id = threadIdx.x; id < (np << lnb); id += blockDim.x) {
+      const int p = id >> lnb, n = id & (g.nbl - 1);
+      const px<T>* s = buf + p * g.rows + (n & 7) * g.bs + (n >> 3) * g.rlp;
+      bfly_px<T, R>([&](int r, int h) { return h ? s[r].b : s[r].a; }, [&](int, cx<T> v) { return v; },
+                    [&](int r, int h, cx<T> v) { put(p, n + r * g.nbl, h, v); });
+    }
+  });
+}
+
+// Depth FFT (any radices) over np pairs, point i of pair p in row(i) at
+// p * rows.  One butterfly of one line per thread, the two lines of a pair in
+// neighbouring lanes: a depth line has few butterflies of a large radix (8 of
+// radix 23 at nz = 184), so the lines, not the pairs, fill the lanes.
+template <typename T, typename Get>
+__device__ __forceinline__ void depth_first(CFft& g, px<T>* z, const cx<T>* tw, int np, Get get) {
+  const int NT = blockDim.x;
+  with_tw_radix(g.r0, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < 2 * np * g.sub0; id += NT) {
+      const int h = id & 1, p = fdiv(id >> 1, g.m_sub0), j = (id >> 1) - p * g.sub0;
+      cx<T>* s = reinterpret_cast<cx<T>*>(z + p * g.rows + j + fdiv(j, g.m_rl) * (g.rlp - g.rl)) + h;
+      cx<T> v[R];
+      get(p, h, j, s, v, tag);
+      dft_emit<T, R>(v, [&](int d, cx<T> x) { s[2 * d * g.bs] = d ? cmul(x, tw[j * d]) : x; });
+    }
+  });
+  __syncthreads();
+}
+template <typename T>
+__device__ __forceinline__ void depth_mid(CFft& g, px<T>* z, const cx<T>* tw, int np) {
+  if (g.r1 == 1) return;
+  const int NT = blockDim.x;
+  with_tw_radix(g.r1, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < 2 * np * g.r0 * g.rl; id += NT) {
+      const int h = id & 1, p = fdiv(id >> 1, g.m_nb1), q = (id >> 1) - p * (g.r0 * g.rl);
+      const int blk = fdiv(q, g.m_rl), j = q - blk * g.rl;
+      cx<T>* s = reinterpret_cast<cx<T>*>(z + p * g.rows + blk * g.bs + j) + h;
+      cx<T> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = s[2 * r * g.rlp];
+      dft_emit<T, R>(v, [&](int d, cx<T> x) { s[2 * d * g.rlp] = d ? cmul(x, tw[j * d * g.r0]) : x; });
+    }
+  });
+  __syncthreads();
+}
+// sink(p, half, n, d, X_k) receives output k = n + d nbl; neighbouring lanes
+// hold neighbouring n
+template <typename T, typename Sink>
+__device__ __forceinline__ void depth_last(CFft& g, const px<T>* z, int np, Sink sink) {
+  const int NT = blockDim.x;
+  with_last_radix(g.rl, [&](auto tag) {
+    constexpr int R = decltype(tag)::v;
+#pragma unroll 1
+    for (int id = threadIdx.x; id < 2 * np * g.nbl; id += NT) {
+      const int h = id & 1, p = fdiv(id >> 1, g.m_nbl), n = (id >> 1) - p * g.nbl;
+      const int d2 = fdiv(n, g.m_r0), d1 = n - d2 * g.r0;
+      const cx<T>* s = reinterpret_cast<const cx<T>*>(z + p * g.rows + d1 * g.bs + d2 * g.rlp) + h;
+      cx<T> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = s[2 * r];
+      auto put = sink(p, h, n);
+      dft_emit<T, R>(v, [&](int d, cx<T> x) { put(d, x); });
+    }
+  });
+}
+
+constexpr int kGTaps = 12;  // taps of the default window (2cK at c = 2, K = 3)
+
+// Sums of one window over both lines of a pair: +nup at up, -nup at un.
+template <typename T, bool REV>
+__device__ __forceinline__ void gpair_sums(const px<T>* up, const px<T>* un, const PairWin<T, kGTaps>& pw, px<T>* sp,
+                                           px<T>* sn) {
+#pragma unroll
+  for (int t = 0; t < kGTaps; ++t) {
+    const px<T> g = up[t], h = un[t];
+    const T w = pw.w[t], b = REV ? pw.w[kGTaps - 1 - t] : bitsel(pw.on, pw.w[t], pw.w[kGTaps - 1 - t]);
+    sp->a.x += w * g.a.x;
+    sp->a.y += w * g.a.y;
+    sp->b.x += w * g.b.x;
+    sp->b.y += w * g.b.y;
+    sn->a.x += b * h.a.x;
+    sn->a.y += b * h.a.y;
+    sn->b.x += b * h.b.x;
+    sn->b.y += b * h.b.y;
+  }
+}
+template <typename T>
+__device__ __forceinline__ void gpair_values(const px<T>* U, int m, const PairWin<T, kGTaps>& pw, px<T>* vp,
+                                             px<T>* vn) {
+  const cx<T> z = mk(T(0), T(0));
+  px<T> sp{z, z}, sn{z, z};
+  if (pw.jp <= m - kGTaps && pw.jn <= m - kGTaps) {
+    if (__any(pw.on)) gpair_sums<T, false>(U + pw.jp, U + pw.jn, pw, &sp, &sn);
+    else gpair_sums<T, true>(U + pw.jp, U + pw.jn, pw, &sp, &sn);
+  } else {
+    // a window runs past the end of the line: wrap its taps
+#pragma unroll
+    for (int t = 0; t < kGTaps; ++t) {
+      int jp = pw.jp + t, jn = pw.jn + t;
+      jp -= jp >= m ? m : 0;
+      jn -= jn >= m ? m : 0;
+      const px<T> g = U[jp], h = U[jn];
+      const T w = pw.w[t], b = bitsel(pw.on, pw.w[t], pw.w[kGTaps - 1 - t]);
+      sp.a.x += w * g.a.x;
+      sp.a.y += w * g.a.y;
+      sp.b.x += w * g.b.x;
+      sp.b.y += w * g.b.y;
+      sn.a.x += b * h.a.x;
+      sn.a.y += b * h.a.y;
+      sn.b.x += b * h.b.x;
+      sn.b.y += b * h.b.y;
+    }
+  }
+  const cx<T> cp = cconj(pw.ph);
+  vp->a = cmul(sp.a, pw.ph);
+  vp->b = cmul(sp.b, pw.ph);
+  vn->a = cmul(sn.a, cp);
+  vn->b = cmul(sn.b, cp);
+}
+
+// pair_window on the internal grid of m points (c_g of them per time bin)
+template <typename T>
+__device__ __forceinline__ void gpair_window(double nup, double c_g, double ck, const StageArgs& a, int m,
+                                             double inv_m, PairWin<T, kGTaps>& pw) {
+  pw.ph = phase_mpi<T>(nup);
+  int j0;
+  const double d = tap_origin(c_g * nup, ck, &j0);
+  pw.on = d == -1.0;
+  tap_weights_pairs<T, kGTaps>(a, (T)(2.0 * d + 1.0), pw.w);
+  pw.jp = wrap_tap<false>(j0, m, inv_m);
+  pw.jn = wrap_tap<false>(pw.on ? -(j0 + kGTaps - 2) : -(j0 + kGTaps - 1), m, inv_m);
+}
+
+template <typename T>
+constexpr int gline_waves() { return sizeof(T) == 4 ? 3 : 2; }
+
+// R and A^T: per item np line pairs.  The first grid stage takes its nonzero
+// inputs (the centred samples: with m >= 2 nt only the inputs 0, 1, 6, 7 of
+// a radix-8 butterfly) from registers that were loaded during the previous
+// item; the last stage brings the grid to natural order in place; the node
+// values go to a region of their own, whose depth FFT writes its outputs to
+// memory.
+template <typename T>
+__global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a) {
+  const int NT = blockDim.x, tid = threadIdx.x;
+  px<T>* buf = reinterpret_cast<px<T>*>(pat_smem);
+  const cx<T> zero = mk(T(0), T(0));
+  px<T> pre[4];
+  // sample of input i of first-stage butterfly j: position j + {0, 1, 6, 7} S
+  // holds sample (position + nt/2) mod m
+  auto sample = [&](CInst& I, int j, int i) {
+    const int S = I.gm.sub0;
+    return i < 2 ? j + i * S + I.nt / 2 : j + (4 + i) * S - I.gm.L + I.nt / 2;
+  };
+  auto fetch = [&](int item) {
+    const int inst = __builtin_amdgcn_readfirstlane(find_inst(a, item));
+    CInst& I = *(CInst*)a.inst[inst];
+    const int p = fdiv(tid, I.gm.m_sub0), j = tid - p * I.gm.sub0;
+    const int P = (item - a.off[inst]) * I.np + p;
+    const bool ok = p < I.np && P < I.npair;
+    const PairLines q = pair_lines(I, ok ? P : 0);
+    const cx<T>* in = static_cast<const cx<T>*>(a.in[inst]);
+    const uint32_t oa = (uint32_t)q.la * (uint32_t)I.nt, ob = (uint32_t)(q.lb < 0 ? 0 : q.lb) * (uint32_t)I.nt;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int n = sample(I, j, i);
+      const bool in_range = ok && n >= 0 && n < I.nt;
+      pre[i].a = in_range ? *at_off(in, (oa + (uint32_t)n) * (uint32_t)sizeof(cx<T>)) : zero;
+      pre[i].b = in_range && q.lb >= 0 ? *at_off(in, (ob + (uint32_t)n) * (uint32_t)sizeof(cx<T>)) : zero;
+    }
+  };
+  int cur = -1;
+  T snr[4] = {T(0), T(0), T(0), T(0)};
+  cx<T> w1 = zero;
+  int item = blockIdx.x;
+  if (item < a.total) fetch(item);
+  for (; item < a.total; item += gridDim.x) {
+    const int inst = __builtin_amdgcn_readfirstlane(find_inst(a, item));
+    CInst& I = *(CInst*)a.inst[inst];
+    CFft &g = I.gm, &gz = I.gz;
+    const int m = g.L, nz = I.nz, half = nz / 2, np = I.np;
+    px<T>* dz = buf + np * g.rows;
+    cx<T>* twz = reinterpret_cast<cx<T>*>(dz + np * gz.rows);
+    cx<T>* tw8 = twz + nz;
+    const int p0 = fdiv(tid, g.m_sub0), j0 = tid - p0 * g.sub0;
+    if (inst != cur) {
+      __syncthreads();
+      const cx<T>* tz = static_cast<const cx<T>*>(I.tw) + gz.tw;
+      const cx<T>* tm = static_cast<const cx<T>*>(I.tw) + g.tw;
+      for (int e = tid; e < nz; e += NT) twz[e] = tz[e];
+      if (tid < g.rl) tw8[tid] = tm[8 * tid];
+      const T* sn = static_cast<const T*>(I.sn_g);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int n = sample(I, j0, i);
+        snr[i] = n >= 0 && n < I.nt ? sn[n] : T(0);
+      }
+      w1 = tm[j0];
+      cur = inst;
+      __syncthreads();
+    }
+    const int P0 = (item - a.off[inst]) * np;
+    const int npi = min(np, I.npair - P0);
+    if (p0 < np) {
+      px<T> v[8];
+      const px<T> pz{zero, zero};
+      auto in = [&](int i) { return px<T>{cscl(pre[i].a, snr[i]), cscl(pre[i].b, snr[i])}; };
+      v[0] = in(0);
+      v[1] = in(1);
+      v[2] = v[3] = v[4] = v[5] = pz;
+      v[6] = in(2);
+      v[7] = in(3);
+      dft_px<T, 8>(v);
+      twiddle_px<T, 8>(v, w1);
+      px<T>* s = buf + p0 * g.rows + j0 + fdiv(j0, g.m_rl) * (g.rlp - g.rl);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) s[r * g.bs] = v[r];
+    }
+    __syncthreads();
+    grid_mid<T>(g, buf, tw8, np);
+    grid_last_natural<T>(g, buf, np);
+    if (item + (int)gridDim.x < a.total) fetch(item + gridDim.x);
+    __syncthreads();
+    {
+      const double inv_m = 1.0 / (double)m, wsc = I.wcoef * I.scale;
+      const int per = a.mode == 0 ? half : half + 1;
+      const uint32_t mper = a.mode == 0 ? I.m_half : I.m_half1;
+#pragma unroll 1
+      for (int e = tid; e < npi * per; e += NT) {
+        const int p = fdiv(e, mper), la = e - p * per + (a.mode == 0 ? 1 : 0);
+        const PairLines q = pair_lines(I, P0 + p);
+        const double bl = I.b * (double)la * (double)la;
+        const px<T>* U = buf + p * g.rows;
+        double nup = sqrt_nt(q.ka + bl);
+        // (the weight, halved on the Nyquist lane, rides on the node phase)
+        const double wla = a.mode == 0 ? wsc * (double)la * (la < half ? 1.0 : 0.5) : 0.5 * I.scale;
+        PairWin<T, kGTaps> pw;
+        gpair_window<T>(nup, I.c_g, I.ck, a, m, inv_m, pw);
+        pw.ph = cscl(pw.ph, T(a.mode == 0 ? wla * rcp_nt(nup) : wla));
+        px<T> vp, vn;
+        gpair_values<T>(U, m, pw, &vp, &vn);
+        if (!q.shared) {
+          nup = sqrt_nt(q.kb + bl);
+          gpair_window<T>(nup, I.c_g, I.ck, a, m, inv_m, pw);
+          pw.ph = cscl(pw.ph, T(a.mode == 0 ? wla * rcp_nt(nup) : wla));
+          px<T> wp, wn;
+          gpair_values<T>(U, m, pw, &wp, &wn);
+          vp.b = wp.b;
+          vn.b = wn.b;
+        }
+        // conjugated into the depth FFT's rows (point l in row l + pad)
+        px<T>* D = dz + p * gz.rows;
+        auto zrow = [&](int l) {
+          const int d1 = fdiv(l, gz.m_sub0), rest = l - d1 * gz.sub0;
+          return d1 * gz.bs + rest + fdiv(rest, gz.m_rl) * (gz.rlp - gz.rl);
+        };
+        const px<T> sum{cconj(cadd(vp.a, vn.a)), cconj(cadd(vp.b, vn.b))};
+        if (a.mode != 0) {
+          D[zrow(la)] = sum;
+          if (la > 0 && la < half) D[zrow(nz - la)] = sum;
+        } else if (la < half) {
+          D[zrow(la)] = px<T>{cconj(vp.a), cconj(vp.b)};
+          D[zrow(nz - la)] = px<T>{cconj(vn.a), cconj(vn.b)};
+        } else {
+          D[zrow(half)] = sum;
+          D[0] = px<T>{zero, zero};  // l = 0 has weight 0
+        }
+      }
+    }
+    __syncthreads();
+    depth_first<T>(gz, dz, twz, npi, [&](int, int, int, const cx<T>* s, cx<T>* v, auto tag) {
+#pragma unroll
+      for (int r = 0; r < decltype(tag)::v; ++r) v[r] = s[2 * r * gz.bs];
+    });
+    depth_mid<T>(gz, dz, twz, npi);
+    cx<T>* out = static_cast<cx<T>*>(a.out[inst]);
+    depth_last<T>(gz, dz, npi, [&](int p, int h, int n) {
+      const int line = pair_line(I, P0 + p, h);
+      const uint32_t o = ((uint32_t)line * (uint32_t)nz + (uint32_t)n) * (uint32_t)sizeof(cx<T>);
+      const uint32_t st = (uint32_t)gz.nbl * (uint32_t)sizeof(cx<T>);
+      return [=](int d, cx<T> v) {
+        if (line >= 0) *at_off(out, o + (uint32_t)d * st) = cconj(v);
+      };
+    });
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Spreading of a line pair by one wavefront, the transpose of the sums above:
+// spread_line_wave (device.h) for both lines of a pair at once.
+
+// Segmented inclusive sums (see WaveSeg) of both halves of the two passes'
+// values, a step as x += on * (x of the source lane) with on = 0 or 1: one
+// multiply-add beside the move instead of an add and a select.  (A value that
+// is not finite spreads over its line here; the line's FFT does so anyway.)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_0(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, true));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_0(double x) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <int BIT, int CTRL, int ROWS, typename T>
+__device__ __forceinline__ void seg_step_px(const WaveSeg& s, px<T>& p, px<T>& m) {
+  if (s.use & BIT) {
+    const T on = (s.on & BIT) ? T(1) : T(0);
+    auto add = [&](T& x) { x = fma(dpp_0<CTRL, ROWS>(x), on, x); };
+    add(p.a.x);
+    add(p.a.y);
+    add(p.b.x);
+    add(p.b.y);
+    add(m.a.x);
+    add(m.a.y);
+    add(m.b.x);
+    add(m.b.y);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void seg_sum_px(const WaveSeg& s, px<T>& p, px<T>& m) {
+  if (!s.use) return;
+  seg_step_px<1, 0x111, 0xf>(s, p, m);
+  seg_step_px<2, 0x112, 0xf>(s, p, m);
+  seg_step_px<4, 0x114, 0xf>(s, p, m);
+  seg_step_px<8, 0x118, 0xf>(s, p, m);
+  seg_step_px<16, 0x142, 0xa>(s, p, m);
+  seg_step_px<32, 0x143, 0xc>(s, p, m);
+}
+template <typename T>
+__device__ __forceinline__ void add_px(px<T>* c, px<T> v) {
+  px<T> o = *c;
+  o.a = cadd(o.a, v.a);
+  o.b = cadd(o.b, v.b);
+  *c = o;
+}
+template <typename T>
+__device__ __forceinline__ px<T> scl_px(px<T> v, T w) {
+  return px<T>{cscl(v.a, w), cscl(v.b, w)};
+}
+__device__ __forceinline__ int lane_get(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
+__device__ __forceinline__ float lane_get(float v, int k) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+__device__ __forceinline__ double lane_get(double v, int k) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, k);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), k);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// One pass of general position: first taps j (monotone over the lanes), cells
+// wrapped, segments that may meet modulo m written one lane at a time.
+template <typename T>
+__device__ __forceinline__ void gspread_pass(px<T>* G, int m, int j, int r, bool act, int nact, px<T> v, const T* w) {
+  const int L = (int)(threadIdx.x & 63);
+  const int jf = lane_get(j, 0), jl = lane_get(j, nact - 1);
+  const bool distinct = (jf > jl ? jf - jl : jl - jf) < m;
+  const WaveSeg sg = pass_segments(j, act);
+  const bool wr = act && sg.tail;
+#pragma unroll
+  for (int t = 0; t < kGTaps; ++t) {
+    px<T> s = scl_px(v, w[t]);
+    seg_sum(sg, s.a.x, s.a.y);
+    seg_sum(sg, s.b.x, s.b.y);
+    int c = r + t;
+    c -= c >= m ? m : 0;
+    if (distinct) {
+      if (wr) add_px(G + c, s);
+    } else {
+      for (int k = 0; k < 64; ++k) {
+        if (wr && L == k) add_px(G + c, s);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+}
+
+// |l| = q0 .. nz/2 of the pair's nodes at nu+^2 = ak + b l^2 into the grid lines
+// G (m pair cells, zeroed by the caller), the halves that `ha`, `hb` select.
+// D: the pair's depth spectra in natural order.
+template <typename T>
+__device__ __forceinline__ void gspread_nodes(CInst& I, const StageArgs& a, int mode, double ak, bool ha, bool hb,
+                                              px<T>* G, const px<T>* D) {
+  const int L = (int)(threadIdx.x & 63);
+  const int m = I.gm.L, nz = I.nz, half = nz / 2;
+  const int q0 = mode == 0 ? 1 : 0, nq = half - q0 + 1;
+  const double wsc = I.wcoef * I.scale, inv_m = 1.0 / (double)m;
+  const cx<T> zero = mk(T(0), T(0));
+#pragma unroll 1
+  for (int base = 0; base < nq; base += 64) {
+    const int nact = min(64, nq - base);
+    const bool act = L < nact;
+    const int la = act ? q0 + base + L : q0;
+    const double nup = sqrt_nt(ak + I.b * (double)la * (double)la);
+    const cx<T> ph = phase_mpi<T>(nup);
+    px<T> qp, qm;
+    double cf;
+    if (mode == 0) {
+      const bool nyq = la == half;
+      qp = D[nyq ? half : la];
+      qm = D[nyq ? half : nz - la];
+      cf = wsc * (double)la * rcp_nt(nup) * (nyq ? 0.5 : 1.0);
+    } else {
+      qp = D[la];
+      if (la != 0 && la != half) {
+        const px<T> o = D[nz - la];
+        qp.a = cadd(qp.a, o.a);
+        qp.b = cadd(qp.b, o.b);
+      }
+      qm = qp;
+      cf = 0.5 * I.scale;
+    }
+    // (values are dropped by selection, not by a factor 0: an infinite one
+    // must not leave a NaN in its neighbour's cells)
+    const T cff = (T)cf;
+    const cx<T> pc = cscl(ph, cff), pcc = cconj(pc);
+    px<T> vp{cmul(cconj(qp.a), pc), cmul(cconj(qp.b), pc)};
+    px<T> vm{cmul(cconj(qm.a), pcc), cmul(cconj(qm.b), pcc)};
+    if (!(act && ha)) vp.a = vm.a = zero;
+    if (!(act && hb)) vp.b = vm.b = zero;
+    int j0;
+    const double d = tap_origin(I.c_g * nup, I.ck, &j0);
+    const bool on = d == -1.0;
+    T w[kGTaps];
+    tap_weights_pairs<T, kGTaps>(a, (T)(2.0 * d + 1.0), w);
+    const int jm = on ? -(j0 + kGTaps - 2) : -(j0 + kGTaps - 1);
+    const int rp = wrap_tap<false>(j0, m, inv_m), rm = wrap_tap<false>(jm, m, inv_m);
+    if (nact <= 2) {
+      // a few nodes, one after the other, one tap per lane
+      for (int k = 0; k < nact; ++k) {
+        const bool onk = lane_get((int)on, k) != 0;
+        T wt = T(0), wu = T(0);
+#pragma unroll
+        for (int i = 0; i < kGTaps; ++i) {
+          const T wi = lane_get(w[i], k);
+          wt = L == i ? wi : wt;
+          wu = L == (onk ? i : kGTaps - 1 - i) ? wi : wu;
+        }
+        px<T> bp{mk(lane_get(vp.a.x, k), lane_get(vp.a.y, k)), mk(lane_get(vp.b.x, k), lane_get(vp.b.y, k))};
+        px<T> bm{mk(lane_get(vm.a.x, k), lane_get(vm.a.y, k)), mk(lane_get(vm.b.x, k), lane_get(vm.b.y, k))};
+        int cp = lane_get(rp, k) + L, cm = lane_get(rm, k) + L;
+        cp -= cp >= m ? m : 0;
+        cm -= cm >= m ? m : 0;
+        if (L < kGTaps) add_px(G + cp, scl_px(bp, wt));
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (L < kGTaps) add_px(G + cm, scl_px(bm, wu));
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      }
+      continue;
+    }
+    const bool anyon = __any(act && on);
+    const int jf = lane_get(j0, 0), jl = lane_get(j0, nact - 1);
+    const WaveSeg sg = pass_segments(j0, act);
+    const bool wr = act && sg.tail;
+    const bool flat = !__any(wr && (rp > m - kGTaps || rm > m - kGTaps));
+    if (!anyon && flat && passes_disjoint<kGTaps>(jf, jl, m)) {
+      // both passes in one round loop (see spread_pair_wave)
+      px<T>* gp = G + rp;
+      px<T>* gm = G + rm;
+#pragma unroll
+      for (int t = 0; t < kGTaps; ++t) {
+        px<T> xp = scl_px(vp, w[t]), xm = scl_px(vm, w[kGTaps - 1 - t]);
+        seg_sum_px(sg, xp, xm);
+        if (wr) {
+          px<T> ca = gp[t], cb = gm[t];
+          ca.a = cadd(ca.a, xp.a);
+          ca.b = cadd(ca.b, xp.b);
+          cb.a = cadd(cb.a, xm.a);
+          cb.b = cadd(cb.b, xm.b);
+          gp[t] = ca;
+          gm[t] = cb;
+        }
+        // the next round's reads come after this round's writes
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      }
+    } else if (!anyon && jl - jf < m) {
+      // windows that wrap, or passes that meet: the same loop, the cells
+      // wrapped, the second pass's cells read after the first's are written
+#pragma unroll
+      for (int t = 0; t < kGTaps; ++t) {
+        px<T> xp = scl_px(vp, w[t]), xm = scl_px(vm, w[kGTaps - 1 - t]);
+        seg_sum_px(sg, xp, xm);
+        int cp = rp + t, cm = rm + t;
+        cp -= cp >= m ? m : 0;
+        cm -= cm >= m ? m : 0;
+        if (wr) add_px(G + cp, xp);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (wr) add_px(G + cm, xm);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      }
+    } else {
+      T wm[kGTaps];
+#pragma unroll
+      for (int t = 0; t < kGTaps; ++t) wm[t] = bitsel(on, w[t], w[kGTaps - 1 - t]);
+      gspread_pass<T>(G, m, j0, rp, act, nact, vp, w);
+      gspread_pass<T>(G, m, jm, rm, act, nact, vm, wm);
+    }
+  }
+}
+
+// R^T and A: per item np line pairs.  Their depth DFTs read the spectra from
+// memory and leave them in natural order in LDS; each wavefront spreads whole
+// pairs into their grid lines (no block barrier inside); the grid DFTs of all
+// pairs run together and the last stage writes the picked, deconvolved
+// samples X_n = s_n conj(G_k), k = (n - nt/2) mod m, to memory.
+template <typename T>
+__global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline1(StageArgs a) {
+  const int NT = blockDim.x, tid = threadIdx.x;
+  px<T>* buf = reinterpret_cast<px<T>*>(pat_smem);
+  const cx<T> zero = mk(T(0), T(0));
+  PAT_G_ITEMS(a)
+  CFft &g = I.gm, &gz = I.gz;
+  const int m = g.L, nz = I.nz, nt = I.nt, np = I.np;
+  px<T>* dz = buf + np * g.rows;
+  cx<T>* twz = reinterpret_cast<cx<T>*>(dz + np * gz.rows);
+  cx<T>* tw8 = twz + nz;
+  __syncthreads();
+  if (fresh) {
+    const cx<T>* tz = static_cast<const cx<T>*>(I.tw) + gz.tw;
+    const cx<T>* tm = static_cast<const cx<T>*>(I.tw) + g.tw;
+    for (int e = tid; e < nz; e += NT) twz[e] = tz[e];
+    if (tid < g.rl) tw8[tid] = tm[8 * tid];
+    __syncthreads();
+  }
+  const int P0 = li * np, npi = min(np, I.npair - P0);
+  const cx<T>* in = static_cast<const cx<T>*>(a.in[inst]);
+  cx<T>* out = static_cast<cx<T>*>(a.out[inst]);
+  // (the depth scratch is the grid region when it is large enough; each pair's
+  // natural-order spectra go to dz)
+  px<T>* zs = buf;
+  depth_first<T>(gz, zs, twz, npi, [&](int p, int h, int j, const cx<T>*, cx<T>* v, auto tag) {
+    const int line = pair_line(I, P0 + p, h);
+    const uint32_t o = ((uint32_t)line * (uint32_t)nz + (uint32_t)j) * (uint32_t)sizeof(cx<T>);
+    const uint32_t st = (uint32_t)gz.sub0 * (uint32_t)sizeof(cx<T>);
+#pragma unroll
+    for (int r = 0; r < decltype(tag)::v; ++r) v[r] = line >= 0 ? *at_off(in, o + (uint32_t)r * st) : zero;
+  });
+  depth_mid<T>(gz, zs, twz, npi);
+  depth_last<T>(gz, zs, npi, [&](int p, int h, int n) {
+    // (an explicit LDS pointer: captured as a generic one its stores stay flat)
+    typedef __attribute__((address_space(3))) cx<T>* LdsPtr;
+    const LdsPtr D = (LdsPtr)(reinterpret_cast<cx<T>*>(dz + p * gz.rows + n) + h);
+    const int st = 2 * gz.nbl;
+    return [=](int d, cx<T> v) { stx(D + d * st, v); };
+  });
+  __syncthreads();
+  for (int e = tid; e < npi * g.rows; e += NT) buf[e] = px<T>{zero, zero};
+  __syncthreads();
+  for (int p = tid >> 6; p < npi; p += NT >> 6) {
+    const PairLines q = pair_lines(I, __builtin_amdgcn_readfirstlane(P0 + p));
+    px<T>* G = buf + p * g.rows;
+    const px<T>* D = dz + p * gz.rows;
+    for (int s = 0; s < (q.shared ? 1 : 2); ++s)
+      gspread_nodes<T>(I, a, a.mode, s ? q.kb : q.ka, s == 0, q.shared || s == 1, G, D);
+  }
+  __syncthreads();
+  {
+    // first grid stage: from natural order into the padded rows
+    const int p0 = fdiv(tid, g.m_sub0), j0 = tid - p0 * g.sub0;
+    const bool act = p0 < npi;
+    px<T> v[8];
+    if (act) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[r] = buf[p0 * g.rows + j0 + r * g.sub0];
+      dft_px<T, 8>(v);
+      twiddle_px<T, 8>(v, (static_cast<const cx<T>*>(I.tw) + g.tw)[j0]);
+    }
+    __syncthreads();
+    if (act) {
+      px<T>* s = buf + p0 * g.rows + j0 + fdiv(j0, g.m_rl) * (g.rlp - g.rl);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) s[r * g.bs] = v[r];
+    }
+  }
+  __syncthreads();
+  grid_mid<T>(g, buf, tw8, npi);
+  const T* sn = static_cast<const T*>(I.sn_g);
+  grid_last_put<T>(g, buf, npi, [&](int p, int k, int h, cx<T> v) {
+    int n = k + nt / 2;
+    n -= n >= m ? m : 0;
+    const int line = pair_line(I, P0 + p, h);
+    if (n < nt && line >= 0)
+      *at_off(out, ((uint32_t)line * (uint32_t)nt + (uint32_t)n) * (uint32_t)sizeof(cx<T>)) = cscl(cconj(v), sn[n]);
+  });
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Launches
+
+namespace {
+
+template <typename Items>
+void count_items(StageArgs& a, Items items) {
+  a.off[0] = 0;
+  for (int i = 0; i < a.n; ++i) a.off[i + 1] = a.off[i] + items(i);
+  a.total = a.off[a.n];
+  a.counter = nullptr;
+}
+
+int cdiv(int x, int y) { return (x + y - 1) / y; }
+
+template <typename F>
+size_t max_bytes(int n, F f) {
+  size_t mx = 0;
+  for (int i = 0; i < n; ++i) mx = f(i) > mx ? f(i) : mx;
+  return mx;
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t General<T>::x1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
+  count_items(a, [&](int i) { return h[i].n2 * cdiv(a.len_nz ? h[i].nz : h[i].nt, 2 * h[i].gtb1); });
+  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gtile(h[i].g1, h[i].gtb1, sizeof(cx<T>)); });
+  return launch_persistent(k_gtr_x1<T>, "dft_x1", a, shm, st, tm);
+}
+
+template <typename T>
+hipError_t General<T>::x2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
+  count_items(a, [&](int i) { return h[i].n2 > 1 ? h[i].h1 * cdiv(a.len_nz ? h[i].nz : h[i].nt, h[i].gtb2) : 0; });
+  const size_t shm = max_bytes(a.n, [&](int i) { return h[i].n2 > 1 ? lds_gtile(h[i].g2, h[i].gtb2, sizeof(cx<T>)) : 0; });
+  return launch_persistent(k_gtr_x2<T>, a.mode ? "idft_x2" : "dft_x2", a, shm, st, tm);
+}
+
+template <typename T>
+hipError_t General<T>::c2r(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
+  count_items(a, [&](int i) { return h[i].n2 * cdiv(a.len_nz ? h[i].nz : h[i].nt, 2 * h[i].gtb1); });
+  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gtile(h[i].g1, h[i].gtb1, sizeof(cx<T>)); });
+  return launch_persistent(k_gtr_c2r<T>, "idft_x1_c2r", a, shm, st, tm);
+}
+
+// Threads of a line kernel: one first-stage butterfly each.
+static int gline_threads(int n, const Inst* h) {
+  int t = 64;
+  for (int i = 0; i < n; ++i) t = h[i].np * h[i].gm.sub0 > t ? h[i].np * h[i].gm.sub0 : t;
+  return (t + 63) / 64 * 64;
+}
+
+template <typename T>
+hipError_t General<T>::line2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
+  count_items(a, [&](int i) { return cdiv(h[i].npair, h[i].np); });
+  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gline(h[i], sizeof(cx<T>)); });
+  return launch_persistent(k_gline2<T>, "nufft_fused", a, shm, st, tm, gline_threads(a.n, h));
+}
+
+template <typename T>
+hipError_t General<T>::line1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
+  count_items(a, [&](int i) { return cdiv(h[i].npair, h[i].np); });
+  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gline(h[i], sizeof(cx<T>)); });
+  return launch_persistent(k_gline1<T>, "nufft_adjoint_fused", a, shm, st, tm, gline_threads(a.n, h));
+}
+
+template struct General<float>;
+template struct General<double>;
+
+}  // namespace pat

@@ -17,12 +17,12 @@ struct StageTimer {
   virtual ~StageTimer() {}
 };
 
-// Two extra streams and three events of one plan, for the batched launch:
+// Three extra streams and four events of one plan, for the batched launch:
 // its radix classes run on their own streams, forked from the caller's
 // stream and joined back into it.
 struct ForkStreams {
-  hipStream_t s[2] = {nullptr, nullptr};
-  hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
+  hipStream_t s[3] = {nullptr, nullptr, nullptr};
+  hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
 // One operator over n instances.  hinst: host copies of the descriptors,

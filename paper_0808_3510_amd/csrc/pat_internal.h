@@ -38,6 +38,27 @@ struct FftDesc {
   int32_t perm;  // element offset of the bin -> position map in the index table
 };
 
+// Division by a constant d >= 2 as a 32-bit multiply-high: n / d for
+// n d < 2^32 is the high word of n (floor(2^32 / d) + 1); 0 stands for d = 1.
+inline uint32_t div_magic(int d) { return d <= 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d) + 1u; }
+
+// One FFT length of the general-length kernels (general.hip): an in-place
+// decimation-in-frequency transform of L = r0 r1 rl points in two or three
+// stages (r1 = 1: two), every radix up to 23 transformed in registers.  In
+// LDS the points are kept in rows: point d1 (r1 rl) + d2 rl + e sits in row
+// d1 bs + d2 rlp + e, with rlp >= rl and bs >= r1 rlp odd, so that lanes that
+// walk the last stage's butterflies or the first stage's digits meet
+// different banks.
+struct GFft {
+  int32_t L, r0, r1, rl;
+  int32_t rlp, bs;  // row strides of the digits d2 and d1
+  int32_t sub0;     // r1 rl: first-stage butterflies
+  int32_t nbl;      // r0 r1: last-stage butterflies
+  int32_t rows;     // r0 bs: rows of one transform
+  int32_t tw;       // element offset of the L roots in the twiddle table
+  uint32_t m_sub0, m_rl, m_r1, m_r0, m_nbl, m_nb1;  // div_magic of sub0, rl, r1, r0, nbl, r0 rl
+};
+
 // Everything a kernel needs about one reconstruction instance.
 struct Inst {
   int32_t n1, n2, nt, nz, m;  // detectors, time samples, depth samples, c*nt
@@ -65,10 +86,22 @@ struct Inst {
   // normalisation.
   double scale;
   FftDesc f1, f2, fm, fz;
+  // General-length kernels: gtr = 1 when they can take the transverse passes,
+  // gln = 1 the fused line stages.  The line kernels run the Kaiser-Bessel sums on
+  // a grid of gm.L = 8 r1 rl >= m points of their own choice (c_g = gm.L / nt)
+  // with the plan's window in grid units; np lines or mirror pairs per item.
+  int32_t gtr, gln;
+  int32_t gtb1, gtb2;        // tile widths (complex columns) of the x1 and x2 passes
+  int32_t np, npair;         // pairs per work item, pairs of the instance
+  uint32_t m_half, m_half1;  // div_magic of nz/2, nz/2 + 1
+  uint32_t m_h2;             // div_magic of n2/2 (pairs per k1)
+  GFft g1, g2, gm, gz;
+  double c_g;
   // device addresses inside this instance's table buffer (set at upload)
   const void* tw;        // cplx<T>[]
   const int32_t* perm;   // int32[]
   const void* sn;        // T[nt]: e^{alpha K} / I0(K sqrt(alpha^2 - theta_n^2))
+  const void* sn_g;      // T[nt]: the same factors for the grid of gm.L points
   const void* poly_c;    // T[taps][deg+1]: tap t as a polynomial in x = 2 (delta - cK) + 1
   // T[(E+1)^3]: cut-off weight by the samples' distances d_i = min(s, n - s)
   // to the data box faces per axis (x1, x2, t), each clamped to E; entry
@@ -129,5 +162,14 @@ inline size_t lds_fused1(const Inst& I, size_t cs) {
   const size_t za = (size_t)I.lpw_a * I.nz;
   return ((size_t)I.m > za ? (size_t)I.m : za) * cs + za * cs + lds_spread_fused(I, cs);
 }
+
+// general-length line kernels: np pairs of grid lines and of depth lines
+// (two complex values per point), the depth roots, the 16 roots of the middle
+// grid stage
+inline size_t lds_gline(const Inst& I, size_t cs) {
+  return ((size_t)I.np * (I.gm.rows + I.gz.rows) * 2 + I.nz + 16) * cs;
+}
+// general-length transverse passes: a tile and the roots
+inline size_t lds_gtile(const GFft& g, int tb, size_t cs) { return ((size_t)g.rows * tb + g.L) * cs; }
 
 }  // namespace pat

@@ -235,6 +235,87 @@ void cutoff_table(double eps, int dim, std::vector<double>* W) {
   }
 }
 
+// Relative cost per point of a register DFT of R points in the general-length
+// kernels (multiply-adds, counted in units of a radix-2 butterfly's).
+int radix_cost(int R) {
+  static const int c[24] = {0, 0, 2, 4, 4, 7, 6, 9, 6, 8, 9, 14, 8, 16, 11, 11, 8, 20, 10, 23, 11, 13, 16, 27};
+  return c[R];
+}
+
+// Radices of a general-length transform of L points: the cheapest r0 r1 rl =
+// L with rl <= 23 and r0, r1 from the set that those kernels carry in twiddled
+// stages; a further stage costs about a radix-16 one (an LDS round trip), and
+// of equal costs the smaller largest radix wins (more butterflies per stage,
+// so more of a workgroup's threads have one).  False when three such stages
+// do not reach L.
+void finish_general(int L, int tw, GFft* g);
+bool plan_general(int L, int tw, GFft* g) {
+  static const int tw_rad[] = {8, 16, 4, 2, 1, 12, 10, 6, 3, 5, 9, 7, 11, 13};
+  int best = 1 << 30;
+  for (int r0 : tw_rad) {
+    if (L % r0) continue;
+    for (int r1 : tw_rad) {
+      if ((L / r0) % r1) continue;
+      const int rl = L / r0 / r1;
+      if (rl < 2 || rl > 23) continue;
+      const int cost = 4 * (radix_cost(r0) + radix_cost(r1) + radix_cost(rl) + (r1 > 1 ? 8 : 0)) +
+                       std::max(r0, std::max(r1, rl));
+      if (cost < best) {
+        best = cost;
+        g->r0 = r0;
+        g->r1 = r1;
+        g->rl = rl;
+      }
+    }
+  }
+  if (best == 1 << 30) return false;
+  finish_general(L, tw, g);
+  return true;
+}
+
+// The fields of *g that follow from its radices.
+void finish_general(int L, int tw, GFft* g) {
+  g->L = L;
+  g->tw = tw;
+  g->rlp = g->rl | 1;
+  g->bs = (g->r1 * g->rlp) | 1;
+  g->sub0 = g->r1 * g->rl;
+  g->nbl = g->r0 * g->r1;
+  g->rows = g->r0 * g->bs;
+  g->m_sub0 = div_magic(g->sub0);
+  g->m_rl = div_magic(g->rl);
+  g->m_r1 = div_magic(g->r1);
+  g->m_r0 = div_magic(g->r0);
+  g->m_nbl = div_magic(g->nbl);
+  g->m_nb1 = div_magic(g->r0 * g->rl);
+}
+
+// The internal grid of the general-length line kernels: the smallest 8 r1 rl
+// >= m with r1 a power of two up to 16 and rl one of 8, 10, 12, 14 (steps of
+// at most 1.25 from 64 points on), 0 above 1792 points.
+int general_grid(int m, int* r1, int* rl) {
+  for (int a = 1; a <= 16; a *= 2)
+    for (int e = 8; e <= 14; e += 2)
+      if (8 * a * e >= m) {
+        *r1 = a;
+        *rl = e;
+        return 8 * a * e;
+      }
+  return 0;
+}
+
+// Tile width of a general-length transverse pass: the widest of 32, 16, 8
+// columns whose tile and twiddles stay within 40 KB of LDS (four workgroups
+// per CU), else the widest that fits at all.
+int general_tile(const GFft& g, size_t cs) {
+  auto lds = [&](int tb) { return ((size_t)g.rows * tb + g.L) * cs; };
+  for (int tb = 32; tb >= 8; tb /= 2)
+    if (lds(tb) <= 40 * 1024) return tb;
+  for (int tb = 8; tb >= 1; tb /= 2)
+    if (lds(tb) <= kLdsMax) return tb;
+  return 0;
+}
+
 bool is_pow2(int L) { return L > 0 && (L & (L - 1)) == 0; }
 
 int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -380,6 +461,14 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
 
   const int n1 = g.nx[0];
   const int n2 = g.ndim == 3 ? g.nx[1] : 1;
+  // The general-length line kernels choose their own grid length for the
+  // default window at c = 2: at K = 3 and the default alpha its truncation
+  // (~1e-11) is far below FP32 rounding and falls as the grid grows, so any
+  // grid of at least 2 nt points gives the same sums; another c, K or alpha
+  // asks for that method's own error and keeps its grid.
+  int gr1 = 0, grl = 0;
+  const bool default_window = kb && g.c == 2.0 && g.K == 3.0 && gin.alpha == 0.0;
+  const int mg = default_window ? general_grid(m, &gr1, &grl) : 0;
   // FFT plans for every distinct length
   const int lens[4] = {n1, n2, m, g.nz};
   std::vector<int> uniq;
@@ -446,6 +535,8 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
     tw_at[i] = tw_elems;
     tw_elems += uniq[i];
   }
+  const size_t twg_at = tw_elems;  // the roots of the internal grid's length
+  if (mg && mg != m) tw_elems += mg;
   off = align256(off + tw_elems * cs);
   const size_t off_perm = off;
   std::vector<size_t> perm_at(uniq.size());
@@ -457,6 +548,8 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
   off = align256(off + perm_elems * sizeof(int32_t));
   const size_t off_sn = off;
   off = align256(off + (size_t)g.nt * rs);
+  const size_t off_sng = off;
+  if (mg && mg != m) off = align256(off + (size_t)g.nt * rs);
   const int deg = prec == PAT_F64 ? kPolyDegD : kPolyDegF;
   std::vector<double> coef;
   I.kind = g.interp;
@@ -481,13 +574,12 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
   const size_t total = off;
 
   p->blob.assign(total, 0);
-  for (size_t i = 0; i < uniq.size(); ++i) {
-    const int L = uniq[i];
+  auto put_roots = [&](int L, size_t at) {
     for (int k = 0; k < L; ++k) {
       // exp(-2 pi i k / L), argument formed from the reduced fraction k/L
       const double ang = 2.0 * kPi * ((double)k / (double)L);
       const double re = std::cos(ang), im = -std::sin(ang);
-      const size_t o = off_tw + (tw_at[i] + k) * cs;
+      const size_t o = off_tw + (at + k) * cs;
       if (prec == PAT_F64) {
         const double v[2] = {re, im};
         put(p->blob, o, v, 2);
@@ -496,6 +588,11 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
         put(p->blob, o, v, 2);
       }
     }
+  };
+  if (mg && mg != m) put_roots(mg, twg_at);
+  for (size_t i = 0; i < uniq.size(); ++i) {
+    const int L = uniq[i];
+    put_roots(L, tw_at[i]);
     const std::vector<int32_t> pos = dif_positions(L, rads[i]);
     put(p->blob, off_perm + perm_at[i] * sizeof(int32_t), pos.data(), pos.size());
   }
@@ -520,18 +617,28 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
   // deconvolution factors e^{alpha K} / I0(K sqrt(alpha^2 - theta_n^2)),
   // theta_n = 2 pi n / nt - pi  (eq. nufft-c with Psi the Kaiser-Bessel window)
   // (1 for the other methods: Psi = 1 there, or no window at all)
-  for (int n = 0; n < g.nt; ++n) {
-    const double th = 2.0 * kPi * ((double)n / (double)g.nt) - kPi;
-    const double z = g.K * std::sqrt(g.alpha * g.alpha - th * th);
-    const double s = kb ? std::exp(g.alpha * g.K - z) / bessel_i0e(z) : 1.0;
-    const size_t o = off_sn + (size_t)n * rs;
-    if (prec == PAT_F64) {
-      put(p->blob, o, &s, 1);
-    } else {
-      const float f = (float)s;
-      put(p->blob, o, &f, 1);
+  // On a grid of cg nt points the window keeps its width in grid cells (K' =
+  // cK / cg, alpha' = alpha cg / c): theta scales by c / cg, and the tap
+  // weights and the scale 1 / (pi c ...) stay as they are.
+  auto put_deconv = [&](double cg, size_t at) {
+    for (int n = 0; n <= g.nt / 2; ++n) {  // (even in n - nt/2)
+      const double th = (2.0 * kPi * ((double)n / (double)g.nt) - kPi) * (g.c / cg);
+      const double z = g.K * std::sqrt(g.alpha * g.alpha - th * th);
+      const double s = kb ? std::exp(g.alpha * g.K - z) / bessel_i0e(z) : 1.0;
+      for (int q : {n, g.nt - n}) {
+        if (q >= g.nt) continue;
+        const size_t o = at + (size_t)q * rs;
+        if (prec == PAT_F64) {
+          put(p->blob, o, &s, 1);
+        } else {
+          const float f = (float)s;
+          put(p->blob, o, &f, 1);
+        }
+      }
     }
-  }
+  };
+  put_deconv(g.c, off_sn);
+  if (mg && mg != m) put_deconv((double)mg / g.nt, off_sng);
   for (size_t i = 0; i < cutw.size(); ++i) {
     const size_t o = off_cut + i * rs;
     if (prec == PAT_F64) {
@@ -550,6 +657,33 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
       put(p->blob, o, &f, 1);
     }
   }
+  // the general-length kernels (see GFft): 32-bit byte offsets inside an array
+  // reach 4 GiB
+  const bool small32 = (size_t)I.lines * std::max(g.nt, g.nz) * cs < (size_t(1) << 32);
+  I.gtr = prec != PAT_F32_BF16GRID && small32 && plan_general(n1, I.f1.tw, &I.g1) &&
+          (n2 == 1 || plan_general(n2, I.f2.tw, &I.g2));
+  if (I.gtr) {
+    I.gtb1 = general_tile(I.g1, cs);
+    I.gtb2 = n2 == 1 ? 1 : general_tile(I.g2, cs);
+    I.gtr = I.gtb1 > 0 && I.gtb2 > 0;
+  }
+  I.npair = n2 == 1 ? I.h1 : I.lines / 2;
+  I.m_half = div_magic(g.nz / 2);
+  I.m_half1 = div_magic(g.nz / 2 + 1);
+  I.m_h2 = div_magic(n2 / 2);
+  if (I.fused && mg && I.poly && small32 && (size_t)I.npair * std::max(1, n2 / 2) < (size_t(1) << 32) &&
+      plan_general(g.nz, I.fz.tw, &I.gz)) {
+    I.gm.r0 = 8;
+    I.gm.r1 = gr1;
+    I.gm.rl = grl;
+    finish_general(mg, mg != m ? (int)twg_at : I.fm.tw, &I.gm);
+    I.c_g = (double)mg / g.nt;
+    // one first-stage butterfly (of a pair) per thread
+    I.np = std::max(1, kBlock / I.gm.sub0);
+    while (I.np > 1 && lds_gline(I, cs) > (prec == PAT_F64 ? 80 : 40) * 1024) --I.np;
+    // (the depth scratch of the type-1 kernel lies in the grid lines)
+    I.gln = lds_gline(I, cs) <= kLdsMax && I.gz.rows <= I.gm.rows ? 1 : 0;
+  }
   // workspace: G (lines x nt), grid (lines x m), F (lines x nz)
   const size_t lines = (size_t)I.lines;
   I.off_g = 0;
@@ -566,6 +700,7 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
   p->off_tw = off_tw;
   p->off_perm = off_perm;
   p->off_sn = off_sn;
+  p->off_sng = mg && mg != m ? off_sng : off_sn;
   p->off_poly = off_poly;
   p->off_cut = off_cut;
   p->table_bytes = total;
@@ -577,6 +712,7 @@ void bind_table(pat_plan* p, void* table_dev) {
   p->inst.tw = base + p->off_tw;
   p->inst.perm = reinterpret_cast<const int32_t*>(base + p->off_perm);
   p->inst.sn = base + p->off_sn;
+  p->inst.sn_g = base + p->off_sng;
   p->inst.poly_c = base + p->off_poly;
   p->inst.cutw = p->inst.cut_e ? base + p->off_cut : nullptr;
   std::memcpy(p->blob.data() + p->off_desc, &p->inst, sizeof(Inst));

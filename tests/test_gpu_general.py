@@ -1,0 +1,105 @@
+"""The general-length kernels (transverse passes and fused line stages of
+every length that is no power of two) against the oracle's direct sums.
+
+The transverse lengths and depth lengths below make every radix from 2 to 23 a
+last stage and every radix of the set a first or middle one; the time lengths
+put the line kernels' own grid (the next 8 r1 rl >= 2 nt) at the smallest and
+the largest point counts, just below and just above a step, and at every
+middle radix.  FP32 1e-5 (the rounding of FFTs of at most 2^11 points and the
+5e-8 weight fit, with a margin of 10), FP64 1e-9 (the window's truncation of
+1e-11, with a margin)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import recon
+from paper_0808_3510_amd import inputs, pat
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+TOL = {"f32": 1e-5, "f64": 1e-9}
+OPS = ["reconstruct", "reconstruct_adjoint", "forward", "forward_adjoint"]
+
+
+def geo(n1, n2, nt, nz):
+    return dict(n1=n1, n2=n2, nt=nt, nz=nz, dx=1.0, dt=0.9, dz=1.1, vs=1.05)
+
+
+def run(op, g, prec, seed):
+    n_in = g["nt"] if op in ("reconstruct", "forward_adjoint") else g["nz"]
+    shape = (g["n1"], g["n2"], n_in) if g["n2"] > 1 else (g["n1"], n_in)
+    x = inputs.random_array(shape, seed)
+    plan = pat.Plan(g["n1"], g["n2"], g["nt"], g["nz"], g["dx"], g["dt"], g["dz"], g["vs"], precision=prec, device=DEV)
+    y = getattr(plan, op)(torch.from_numpy(x).to(DEV, torch.float64 if prec == "f64" else torch.float32))
+    torch.cuda.synchronize()
+    got, exp = y.cpu().double().numpy(), getattr(recon, op)(x, g)
+    rel = np.linalg.norm(got - exp) / np.linalg.norm(exp)
+    mx = np.abs(got - exp).max() / np.abs(exp).max()
+    print(f"  {op} {prec} {g}: relL2 {rel:.2e}, max {mx:.2e}", flush=True)
+    assert rel <= TOL[prec] and mx <= TOL[prec], (rel, mx)
+
+
+# (n1, n2, nt, nz): last radices of n1, n2 and nz over 2 .. 23, two and three
+# stages, tiles with a remainder of one column pair
+LENGTHS = [(2, 6, 30, 10), (14, 10, 26, 14), (22, 26, 44, 46), (46, 38, 34, 34), (34, 18, 50, 38), (12, 20, 70, 30),
+           (36, 42, 66, 50), (110, 2, 60, 22), (4, 250, 36, 18), (2, 338, 18, 6), (242, 4, 20, 26), (144, 8, 36, 20),
+           (6, 176, 36, 42), (4, 136, 68, 18), (152, 2, 36, 14), (2, 184, 72, 36), (1000, 2, 6, 10), (2, 1536, 10, 6),
+           (54, 2, 20, 52), (2, 98, 20, 90), (182, 2, 18, 162), (2, 70, 18, 96), (130, 4, 10, 120), (312, 2, 6, 64),
+           (416, 2, 6, 16), (420, 2, 6, 150), (196, 2, 6, 200), (384, 2, 6, 210), (306, 2, 6, 128), (374, 2, 6, 30),
+           (672, 2, 6, 50)]
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("op", OPS)
+@pytest.mark.parametrize("n1,n2,nt,nz", LENGTHS)
+def test_transverse_and_depth_lengths(n1, n2, nt, nz, op, prec):
+    run(op, geo(n1, n2, nt, nz), prec, 1200 + n1)
+
+
+# (nt, nz): grids 8 r1 rl of 64 .. 1792 points, at, just below and just above a step
+TIMES = [(6, 4), (32, 18), (34, 18), (40, 22), (48, 26), (60, 32), (72, 38), (100, 52), (128, 66), (150, 76),
+         (208, 104), (256, 130), (300, 150), (440, 220), (500, 252), (640, 320), (770, 384), (896, 448), (900, 450)]
+
+
+@pytest.mark.parametrize("op", OPS)
+@pytest.mark.parametrize("n1,n2", [(6, 10), (10, 1)])
+@pytest.mark.parametrize("nt,nz", TIMES)
+def test_grid_lengths(nt, nz, n1, n2, op):
+    run(op, geo(n1, n2, nt, nz), "f32", 1300 + nt)
+
+
+@pytest.mark.parametrize("op", OPS)
+@pytest.mark.parametrize("nt,nz", [(6, 2), (46, 138), (500, 126), (896, 448), (300, 300)])
+def test_grid_lengths_fp64(nt, nz, op):
+    """(Also nz > nt: depth lines longer than the grid's time lines.)"""
+    run(op, geo(6, 6, nt, nz), "f64", 1400 + nt)
+
+
+def test_nonfinite_values_stay_in_their_lines():
+    """An infinite sample spoils what its transforms reach, as before, and no
+    more: a batch neighbour keeps its values."""
+    g = geo(10, 6, 40, 12)
+    mk = lambda: pat.Plan(g["n1"], g["n2"], g["nt"], g["nz"], precision="f32", device=DEV)  # noqa: E731
+    a, b = mk(), mk()
+    x = torch.from_numpy(inputs.random_array((10, 6, 40), 1500)).to(DEV, torch.float32)
+    y = x.clone()
+    y[3, 2, 7] = float("inf")
+    fa = a.reconstruct(x).clone()
+    (o1, o2), _ = pat.reconstruct_batched([a, b], [x, y])
+    assert torch.equal(o1, fa)
+    assert not torch.isfinite(o2).all()
+
+
+def test_batch_of_mixed_lengths_matches_single_calls():
+    """Instances of different lengths in one launch: each equals its single
+    call bit for bit (lengths that are no powers of two), whatever their
+    order and number."""
+    sizes = [(24, 20, 48, 24), (10, 6, 500, 36), (46, 38, 38, 34), (6, 4, 10, 6), (12, 1, 300, 90), (24, 20, 48, 24)]
+    plans = [pat.Plan(a, b, t, z, precision="f32", device=DEV) for a, b, t, z in sizes]
+    xs = [torch.from_numpy(inputs.random_array((a, b, t) if b > 1 else (a, t), 1600 + i)).to(DEV, torch.float32)
+          for i, (a, b, t, z) in enumerate(sizes)]
+    ref = [p.reconstruct(x).clone() for p, x in zip(plans, xs)]
+    for order in ([0, 1, 2, 3, 4, 5], [4, 3, 0], [5, 1]):
+        outs, _ = pat.reconstruct_batched([plans[i] for i in order], [xs[i] for i in order])
+        for i, o in zip(order, outs):
+            assert torch.equal(o, ref[i]), sizes[i]
