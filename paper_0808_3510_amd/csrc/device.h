@@ -707,6 +707,8 @@ struct StageArgs {
   int32_t item_slot;  // with a counter: byte offset of the item slot in dynamic LDS
   int32_t len_nz;     // transverse passes: lines have nz (else nt) samples
   int32_t mode;       // FFT direction (0 forward, 1 inverse) / interp, spread mode
+  int32_t np_cap;     // general-length kernels: upper bounds on the pairs per item and
+  int32_t tb_cap;     // on the tile width for this launch (0: the plan's own)
   int32_t pair_ok;    // pc holds every instance's mirrored tap-pair polynomials
   // per tap pair p (taps t = p and taps-1-p): even part (powers x^0, x^2, ...)
   // then odd part (x^1, x^3, ...) of tap p's polynomial, in the compute type
@@ -1828,7 +1830,7 @@ __device__ __forceinline__ void cut_pair(const Inst& I, const T* ws, int b2, int
 // Host launchers (the functions are in kernels.hip)
 
 int num_cu();
-int resident_blocks(const void* kernel, size_t shmem, int block = kBlock);
+int resident_blocks(const void* kernel, size_t shmem, int block, hipError_t* err);
 bool launch_faulted();
 
 template <typename K>
@@ -1839,18 +1841,19 @@ hipError_t launch(K kernel, const char* name, StageArgs& a, size_t shmem, hipStr
     a.item_slot = (int32_t)((shmem + 15) & ~(size_t)15);
     shmem = (size_t)a.item_slot + 16;
   }
-  if (shmem > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return e;
-  }
   // one workgroup per item; with a work counter, a persistent grid of as many
   // workgroups as fit on the device at once
-  const int cap = a.counter ? resident_blocks(reinterpret_cast<const void*>(kernel), shmem) * num_cu() : a.total;
+  hipError_t e = hipSuccess;
+  int cap = a.total;
+  if (a.counter || shmem > 65536) {
+    const int per_cu = resident_blocks(reinterpret_cast<const void*>(kernel), shmem, kBlock, &e);
+    if (e != hipSuccess) return e;
+    if (a.counter) cap = per_cu * num_cu();
+  }
   const int grid = a.total < cap ? a.total : cap;
   if (tm) tm->begin(name, st);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), shmem, st, a);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (tm) tm->end(st);
   return e;
 }
@@ -1862,16 +1865,13 @@ hipError_t launch_persistent(K kernel, const char* name, StageArgs& a, size_t sh
                              StageTimer* tm, int block = kBlock) {
   if (a.total <= 0) return hipSuccess;
   if (launch_faulted()) return hipErrorLaunchFailure;
-  if (shmem > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return e;
-  }
-  const int cap = resident_blocks(reinterpret_cast<const void*>(kernel), shmem, block) * num_cu();
+  hipError_t e = hipSuccess;
+  const int cap = resident_blocks(reinterpret_cast<const void*>(kernel), shmem, block, &e) * num_cu();
+  if (e != hipSuccess) return e;
   const int grid = a.total < cap ? a.total : cap;
   if (tm) tm->begin(name, st);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), shmem, st, a);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (tm) tm->end(st);
   return e;
 }

@@ -17,4 +17,17 @@ struct General {
   static hipError_t line1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm);
 };
 
+// The transverse passes of one instance at 128, 256 and 512 points, sizes
+// fixed at compile time (transverse.hip).
+template <typename T>
+struct Fixed {
+  // Length L on `rows` lines of len samples, where its tiles of 32 samples give
+  // every CU one (below that the general-length kernels' narrower tiles take
+  // less time).
+  static bool takes(int L, int rows, int len);
+  static hipError_t x1(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);
+  static hipError_t x2(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);
+  static hipError_t c2r(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);
+};
+
 }  // namespace pat

@@ -15,212 +15,9 @@
 // two-stage length crosses LDS once.  The last stage has no twiddles, and the
 // plan puts the large primes there.
 #include "general.h"
+#include "regfft.h"
 
 namespace pat {
-
-// Descriptors are read through the constant address space: their fields then
-// come by scalar loads, once, whatever the kernel stores in between (through a
-// plain pointer they were vector loads, repeated after every barrier: the
-// fused type-2 kernel took 79 instead of XX us at 152 x 136 x 368).
-using CInst = const __attribute__((address_space(4))) Inst;
-using CFft = const __attribute__((address_space(4))) GFft;
-
-__device__ __forceinline__ int fdiv(int n, uint32_t m) { return m ? (int)__umulhi((unsigned)n, m) : n; }
-
-// ---------------------------------------------------------------------------
-// R-point DFTs in registers, natural order in and out.
-
-template <typename T, int R>
-__device__ __forceinline__ void dft_reg(cx<T>* v);
-
-// odd prime, by the symmetric form of bfly_prime with every root a constant
-template <typename T, int R>
-__device__ __forceinline__ void dft_prime(cx<T>* v) {
-  constexpr int H = (R - 1) / 2;
-  cx<T> av[H], bv[H];
-  const cx<T> x0 = v[0];
-  cx<T> s = x0;
-#pragma unroll
-  for (int r = 1; r <= H; ++r) {
-    av[r - 1] = cadd(v[r], v[R - r]);
-    bv[r - 1] = csub(v[r], v[R - r]);
-    s = cadd(s, av[r - 1]);
-  }
-  v[0] = s;
-#pragma unroll
-  for (int d = 1; d <= H; ++d) {
-    cx<T> A = x0, B = mk(T(0), T(0));
-#pragma unroll
-    for (int r = 1; r <= H; ++r) {
-      const T c = T(Roots<R>::t.c[(r * d) % R]), sn = T(Roots<R>::t.s[(r * d) % R]);
-      A.x += av[r - 1].x * c;
-      A.y += av[r - 1].y * c;
-      B.x += bv[r - 1].x * sn;
-      B.y += bv[r - 1].y * sn;
-    }
-    v[d] = mk(A.x + B.y, A.y - B.x);
-    v[R - d] = mk(A.x - B.y, A.y + B.x);
-  }
-}
-
-// R = A B with coprime factors (prime-factor map): input n = B n1 + A n2,
-// output k with k = k1 mod A, k = k2 mod B; no twiddles
-constexpr int crt(int A, int B, int k1, int k2) {
-  for (int k = 0; k < A * B; ++k)
-    if (k % A == k1 && k % B == k2) return k;
-  return 0;
-}
-template <typename T, int A, int B>
-__device__ __forceinline__ void dft_pfa(cx<T>* v) {
-  cx<T> t[A][B];
-#pragma unroll
-  for (int i = 0; i < A; ++i) {
-#pragma unroll
-    for (int j = 0; j < B; ++j) t[i][j] = v[(B * i + A * j) % (A * B)];
-    dft_reg<T, B>(t[i]);
-  }
-#pragma unroll
-  for (int j = 0; j < B; ++j) {
-    cx<T> u[A];
-#pragma unroll
-    for (int i = 0; i < A; ++i) u[i] = t[i][j];
-    dft_reg<T, A>(u);
-#pragma unroll
-    for (int i = 0; i < A; ++i) v[crt(A, B, i, j)] = u[i];
-  }
-}
-
-// 9 = 3 x 3 with the roots of 9 between the two steps
-template <typename T>
-__device__ __forceinline__ void dft_9(cx<T>* v) {
-  cx<T> t[3][3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-#pragma unroll
-    for (int j = 0; j < 3; ++j) t[i][j] = v[3 * j + i];
-    dft_reg<T, 3>(t[i]);
-  }
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    cx<T> u[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const T c = T(Roots<9>::t.c[i * j]), s = T(Roots<9>::t.s[i * j]);
-      u[i] = mk(t[i][j].x * c + t[i][j].y * s, t[i][j].y * c - t[i][j].x * s);
-    }
-    dft_reg<T, 3>(u);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) v[3 * i + j] = u[i];
-  }
-}
-
-template <typename T, int R>
-__device__ __forceinline__ void dft_reg(cx<T>* v) {
-  if constexpr (R == 1) {
-  } else if constexpr (R == 2 || R == 4 || R == 8 || R == 16) dft_pow2<T, R>(v);
-  else if constexpr (R == 9) dft_9<T>(v);
-  else if constexpr (R == 6) dft_pfa<T, 2, 3>(v);
-  else if constexpr (R == 10) dft_pfa<T, 2, 5>(v);
-  else if constexpr (R == 12) dft_pfa<T, 4, 3>(v);
-  else if constexpr (R == 14) dft_pfa<T, 2, 7>(v);
-  else if constexpr (R == 15) dft_pfa<T, 3, 5>(v);
-  else if constexpr (R == 18) dft_pfa<T, 2, 9>(v);
-  else if constexpr (R == 20) dft_pfa<T, 4, 5>(v);
-  else if constexpr (R == 21) dft_pfa<T, 3, 7>(v);
-  else if constexpr (R == 22) dft_pfa<T, 2, 11>(v);
-  else dft_prime<T, R>(v);
-}
-
-// The R outputs of a butterfly handed to emit(k, X_k): the larger primes one
-// output pair at a time (their R outputs beside the R combined inputs would
-// not fit in registers), the others after the whole transform.
-template <typename T, int R, typename Emit>
-__device__ __forceinline__ void dft_emit(cx<T>* v, Emit emit) {
-  if constexpr (R == 13 || R == 17 || R == 19 || R == 23) {
-    constexpr int H = (R - 1) / 2;
-    cx<T> s = v[0];
-#pragma unroll
-    for (int r = 1; r <= H; ++r) {
-      const cx<T> p = cadd(v[r], v[R - r]);
-      v[R - r] = csub(v[r], v[R - r]);
-      v[r] = p;
-      s = cadd(s, p);
-    }
-    emit(0, s);
-#pragma unroll
-    for (int d = 1; d <= H; ++d) {
-      cx<T> A = v[0], B = mk(T(0), T(0));
-#pragma unroll
-      for (int r = 1; r <= H; ++r) {
-        const T c = T(Roots<R>::t.c[(r * d) % R]), sn = T(Roots<R>::t.s[(r * d) % R]);
-        A.x += v[r].x * c;
-        A.y += v[r].y * c;
-        B.x += v[R - r].x * sn;
-        B.y += v[R - r].y * sn;
-      }
-      emit(d, mk(A.x + B.y, A.y - B.x));
-      emit(R - d, mk(A.x - B.y, A.y + B.x));
-    }
-  } else {
-    dft_reg<T, R>(v);
-#pragma unroll
-    for (int d = 0; d < R; ++d) emit(d, v[d]);
-  }
-}
-
-// f.operator()<R>() for the run-time radix r of a twiddled stage (the set
-// plan_general takes r0 and r1 from) and of a last stage
-template <int R>
-struct RadixTag {
-  static constexpr int v = R;
-};
-#define PAT_CASE(R) \
-  case R: f(RadixTag<R>{}); break;
-template <typename F>
-__device__ __forceinline__ void with_tw_radix(int r, F f) {
-  switch (r) {
-    PAT_CASE(1) PAT_CASE(2) PAT_CASE(3) PAT_CASE(4) PAT_CASE(5) PAT_CASE(6) PAT_CASE(7) PAT_CASE(8) PAT_CASE(9)
-    PAT_CASE(10) PAT_CASE(11) PAT_CASE(12) PAT_CASE(13) PAT_CASE(16)
-    default: break;
-  }
-}
-template <typename F>
-__device__ __forceinline__ void with_last_radix(int r, F f) {
-  switch (r) {
-    PAT_CASE(2) PAT_CASE(3) PAT_CASE(4) PAT_CASE(5) PAT_CASE(6) PAT_CASE(7) PAT_CASE(8) PAT_CASE(9) PAT_CASE(10)
-    PAT_CASE(11) PAT_CASE(12) PAT_CASE(13) PAT_CASE(14) PAT_CASE(15) PAT_CASE(16) PAT_CASE(17) PAT_CASE(18)
-    PAT_CASE(19) PAT_CASE(20) PAT_CASE(21) PAT_CASE(22) PAT_CASE(23)
-    default: break;
-  }
-}
-
-// element at a 32-bit byte offset from a workgroup-uniform base
-template <typename V>
-__device__ __forceinline__ V* at_off(V* base, uint32_t bytes) {
-  using C = std::conditional_t<std::is_const_v<V>, const char, char>;
-  return reinterpret_cast<V*>(reinterpret_cast<C*>(base) + bytes);
-}
-
-template <typename T, bool NT>
-__device__ __forceinline__ cx<T> ld_cx(const cx<T>* p) {
-  if constexpr (NT && sizeof(T) == 4) {
-    typedef float v2f __attribute__((ext_vector_type(2)));
-    const v2f v = __builtin_nontemporal_load(reinterpret_cast<const v2f*>(p));
-    return mk(v.x, v.y);
-  } else {
-    return *p;
-  }
-}
-template <typename T, bool NT>
-__device__ __forceinline__ void st_cx(cx<T>* p, cx<T> v) {
-  if constexpr (NT && sizeof(T) == 4) {
-    typedef float v2f __attribute__((ext_vector_type(2)));
-    const v2f u = {v.x, v.y};
-    __builtin_nontemporal_store(u, reinterpret_cast<v2f*>(p));
-  } else {
-    *p = v;
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Transverse passes: tiles of tb columns (a power of two; the contiguous t or
@@ -233,7 +30,7 @@ __device__ __forceinline__ void gtr_first(CFft& g, cx<T>* buf, const cx<T>* tw, 
   with_tw_radix(g.r0, [&](auto tag) {
     constexpr int R = decltype(tag)::v;
 #pragma unroll 1
-    for (int id = threadIdx.x; id < total; id += kBlock) {
+    for (int id = threadIdx.x; id < total; id += (int)blockDim.x) {
       const int col = id & (tb - 1), j = id >> ltb;
       cx<T> v[R];
 #pragma unroll
@@ -255,7 +52,7 @@ __device__ __forceinline__ void gtr_mid(CFft& g, cx<T>* buf, const cx<T>* tw, in
   with_tw_radix(g.r1, [&](auto tag) {
     constexpr int R = decltype(tag)::v;
 #pragma unroll 1
-    for (int id = threadIdx.x; id < total; id += kBlock) {
+    for (int id = threadIdx.x; id < total; id += (int)blockDim.x) {
       const int col = id & (tb - 1), bf = id >> ltb;
       const int blk = fdiv(bf, g.m_rl), j = bf - blk * g.rl;
       cx<T>* p = buf + ((blk * g.bs + j) << ltb) + col;
@@ -276,7 +73,7 @@ __device__ __forceinline__ void gtr_last(CFft& g, const cx<T>* buf, int ltb, Sto
   with_last_radix(g.rl, [&](auto tag) {
     constexpr int R = decltype(tag)::v;
 #pragma unroll 1
-    for (int id = threadIdx.x; id < total; id += kBlock) {
+    for (int id = threadIdx.x; id < total; id += (int)blockDim.x) {
       const int col = id & (tb - 1), bf = id >> ltb;
       const int d1 = fdiv(bf, g.m_r1), d2 = bf - d1 * g.r1;
       const cx<T>* p = buf + ((d1 * g.bs + d2 * g.rlp) << ltb) + col;
@@ -289,17 +86,10 @@ __device__ __forceinline__ void gtr_last(CFft& g, const cx<T>* buf, int ltb, Sto
   });
 }
 
+__host__ __device__ __forceinline__ int capped(int v, int cap) { return cap && cap < v ? cap : v; }
+
 template <typename T>
 constexpr int gtr_waves() { return sizeof(T) == 4 ? 4 : 2; }
-
-// Item of slot i: workgroups go to the eight XCDs in turn, so slot i runs on
-// XCD i mod 8; each XCD gets one contiguous run of items, whose neighbours (tiles
-// that share cache lines where a row is no multiple of a line) then meet in
-// its L2.
-__device__ __forceinline__ int xcd_item(int i, int total) {
-  const int q = total >> 3, r = total & 7, x = i & 7;
-  return x * q + min(x, r) + (i >> 3);
-}
 
 // Loop over the items of a persistent grid: item, its instance I and its index
 // li within the instance; `fresh` when the instance differs from the last.
@@ -316,24 +106,43 @@ __device__ __forceinline__ int xcd_item(int i, int total) {
 template <typename T>
 __device__ __forceinline__ void g_roots(cx<T>* dst, CInst& I, CFft& g) {
   const cx<T>* src = static_cast<const cx<T>*>(I.tw) + g.tw;
-  for (int e = threadIdx.x; e < g.L; e += kBlock) dst[e] = src[e];
+  for (int e = threadIdx.x; e < g.L; e += (int)blockDim.x) dst[e] = src[e];
 }
 
+// Cut-off weights of one column x2 of the data-side passes: the slice
+// W[b1][b(x2)][b3] in LDS, and the weights of the samples t and t + 1 of row x
+// (see cut_slice, cut_pair).
 template <typename T>
+__device__ __forceinline__ void g_cut_slice(CInst& I, T* ws, int x2) {
+  const int E = I.cut_e, e1 = E + 1, b2 = I.n2 > 1 ? cut_band(x2, I.n2, E) : E;
+  const T* W = static_cast<const T*>(I.cutw);
+  for (int e = threadIdx.x; e < e1 * e1; e += (int)blockDim.x) {
+    const int b1 = e / e1, b3 = e - b1 * e1;
+    ws[e] = W[(b1 * e1 + b2) * e1 + b3];
+  }
+}
+template <typename T>
+__device__ __forceinline__ cx<T> g_cut(CInst& I, const T* ws, int x, int t, int len, cx<T> v) {
+  const T* w = ws + cut_band(x, I.n1, I.cut_e) * (I.cut_e + 1);
+  return mk(v.x * w[cut_band(t, len, I.cut_e)], v.y * w[cut_band(t + 1, len, I.cut_e)]);
+}
+
+template <typename T, bool CUT>
 __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x1(StageArgs a) {
   PAT_G_ITEMS(a)
   CFft& g = I.g1;
   cx<T>* tw = reinterpret_cast<cx<T>*>(pat_smem);
   cx<T>* buf = tw + g.L;
-  __syncthreads();
-  if (fresh) {
-    g_roots(tw, I, g);
-    __syncthreads();
-  }
   const int len = a.len_nz ? I.nz : I.nt;  // even
-  const int tb = I.gtb1, ltb = __builtin_ctz((unsigned)tb);
+  const int tb = capped(I.gtb1, a.tb_cap), ltb = __builtin_ctz((unsigned)tb);
   const int ntile = (len + 2 * tb - 1) / (2 * tb);
   const int x2 = li / ntile;
+  const bool cut = CUT && I.cut_e;
+  T* cws = reinterpret_cast<T*>(buf + g.rows * tb);
+  __syncthreads();
+  if (fresh) g_roots(tw, I, g);
+  if (cut) g_cut_slice(I, cws, x2);
+  if (fresh || cut) __syncthreads();
   const int t0 = (li - x2 * ntile) * 2 * tb;
   const size_t base = (size_t)x2 * len + t0;
   const cx<T>* in = reinterpret_cast<const cx<T>*>(static_cast<const T*>(a.in[inst]) + base);
@@ -342,15 +151,16 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x1(StageArgs a) 
   const int w = (len - t0) >> 1;  // columns of this tile
   // complex column b holds the samples t0 + 2b (real part) and t0 + 2b + 1
   gtr_first<T>(g, buf, tw, ltb, [&](int x, int b) {
-    return b < w ? ld_cx<T, true>(at_off(in, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)))
-                 : mk(T(0), T(0));
+    const cx<T> v = b < w ? ld_cx<T, true>(at_off(in, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)))
+                          : mk(T(0), T(0));
+    return cut ? g_cut(I, cws, x, min(t0 + 2 * b, len - 2), len, v) : v;
   });
   gtr_mid<T>(g, buf, tw, ltb);
   // in place: output r of a butterfly goes to the row its input r came from
   with_last_radix(g.rl, [&](auto tag) {
     constexpr int R = decltype(tag)::v;
 #pragma unroll 1
-    for (int id = threadIdx.x; id < (g.nbl << ltb); id += kBlock) {
+    for (int id = threadIdx.x; id < (g.nbl << ltb); id += (int)blockDim.x) {
       const int col = id & (tb - 1), bf = id >> ltb;
       const int d1 = fdiv(bf, g.m_r1), d2 = bf - d1 * g.r1;
       cx<T>* p = buf + ((d1 * g.bs + d2 * g.rlp) << ltb) + col;
@@ -366,8 +176,8 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x1(StageArgs a) 
   // k = n + d nbl of one butterfly n and the outputs of its mirror butterfly
   // (their LDS rows differ by one per step).
   const int nb = g.nbl << ltb, half = g.L / 2;
-  const int nq = nb < kBlock ? kBlock / nb : 1;  // threads per butterfly
-  for (int id = threadIdx.x; id < nb * nq; id += kBlock) {
+  const int nq = nb < (int)blockDim.x ? (int)blockDim.x / nb : 1;  // threads per butterfly
+  for (int id = threadIdx.x; id < nb * nq; id += (int)blockDim.x) {
     const int b = id & (tb - 1), q = fdiv(id >> ltb, g.m_nbl), n = (id >> ltb) - q * g.nbl;
     if (b >= w) continue;
     const int nm = n ? g.nbl - n : 0;
@@ -401,7 +211,7 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x2(StageArgs a) 
     __syncthreads();
   }
   const int len = a.len_nz ? I.nz : I.nt;
-  const int tb = I.gtb2, ltb = __builtin_ctz((unsigned)tb);
+  const int tb = capped(I.gtb2, a.tb_cap), ltb = __builtin_ctz((unsigned)tb);
   const int ntile = (len + tb - 1) / tb;
   const int k1 = li / ntile;
   const int t0 = (li - k1 * ntile) * tb;
@@ -420,21 +230,22 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_x2(StageArgs a) 
   }
 }
 
-template <typename T>
+template <typename T, bool CUT>
 __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_c2r(StageArgs a) {
   PAT_G_ITEMS(a)
   CFft& g = I.g1;
   cx<T>* tw = reinterpret_cast<cx<T>*>(pat_smem);
   cx<T>* buf = tw + g.L;
-  __syncthreads();
-  if (fresh) {
-    g_roots(tw, I, g);
-    __syncthreads();
-  }
   const int len = a.len_nz ? I.nz : I.nt;
-  const int tb = I.gtb1, ltb = __builtin_ctz((unsigned)tb);
+  const int tb = capped(I.gtb1, a.tb_cap), ltb = __builtin_ctz((unsigned)tb);
   const int ntile = (len + 2 * tb - 1) / (2 * tb);
   const int x2 = li / ntile;
+  const bool cut = CUT && I.cut_e;
+  T* cws = reinterpret_cast<T*>(buf + g.rows * tb);
+  __syncthreads();
+  if (fresh) g_roots(tw, I, g);
+  if (cut) g_cut_slice(I, cws, x2);
+  if (fresh || cut) __syncthreads();
   const int t0 = (li - x2 * ntile) * 2 * tb;
   const size_t base = (size_t)x2 * len + t0;
   const cx<T>* in = static_cast<const cx<T>*>(a.in[inst]) + base;
@@ -456,7 +267,9 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_c2r(StageArgs a)
   });
   gtr_mid<T>(g, buf, tw, ltb);
   gtr_last<T>(g, buf, ltb, [&](int x, int b, cx<T> v) {
-    if (b < w) st_cx<T, true>(at_off(out, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)), mk(v.x, -v.y));
+    cx<T> y = mk(v.x, -v.y);
+    if (cut) y = g_cut(I, cws, x, min(t0 + 2 * b, len - 2), len, y);
+    if (b < w) st_cx<T, true>(at_off(out, (uint32_t)x * row + (uint32_t)b * (uint32_t)sizeof(cx<T>)), y);
   });
   }
 }
@@ -565,7 +378,7 @@ __device__ __forceinline__ void bfly_px(Get get, Tw tw, Put put) {
 }
 
 // Stages of the grid FFT (r0 = 8, r1 a power of two, rl one of 8, 10, 12,
-// 14) over the np pairs of an item.  Pair p's points sit at p * rows, point i
+// 14, 16) over the np pairs of an item.  Pair p's points sit at p * rows, point i
 // in row d1 bs + d2 rlp + e (see GFft); NT threads.
 template <typename T>
 __device__ __forceinline__ void grid_mid(CFft& g, px<T>* buf, const cx<T>* tw8, int np) {
@@ -616,7 +429,7 @@ __device__ __forceinline__ void grid_mid(CFft& g, px<T>* buf, const cx<T>* tw8, 
 template <typename F>
 __device__ __forceinline__ void with_grid_radix(int r, F f) {
   switch (r) {
-    PAT_CASE(8) PAT_CASE(10) PAT_CASE(12) PAT_CASE(14)
+    PAT_CASE(8) PAT_CASE(10) PAT_CASE(12) PAT_CASE(14) PAT_CASE(16)
     default: break;
   }
 }
@@ -811,9 +624,9 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a
   auto fetch = [&](int item) {
     const int inst = __builtin_amdgcn_readfirstlane(find_inst(a, item));
     CInst& I = *(CInst*)a.inst[inst];
-    const int p = fdiv(tid, I.gm.m_sub0), j = tid - p * I.gm.sub0;
-    const int P = (item - a.off[inst]) * I.np + p;
-    const bool ok = p < I.np && P < I.npair;
+    const int p = fdiv(tid, I.gm.m_sub0), j = tid - p * I.gm.sub0, np = capped(I.np, a.np_cap);
+    const int P = (item - a.off[inst]) * np + p;
+    const bool ok = p < np && P < I.npair;
     const PairLines q = pair_lines(I, ok ? P : 0);
     const cx<T>* in = static_cast<const cx<T>*>(a.in[inst]);
     const uint32_t oa = (uint32_t)q.la * (uint32_t)I.nt, ob = (uint32_t)(q.lb < 0 ? 0 : q.lb) * (uint32_t)I.nt;
@@ -834,7 +647,7 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a
     const int inst = __builtin_amdgcn_readfirstlane(find_inst(a, item));
     CInst& I = *(CInst*)a.inst[inst];
     CFft &g = I.gm, &gz = I.gz;
-    const int m = g.L, nz = I.nz, half = nz / 2, np = I.np;
+    const int m = g.L, nz = I.nz, half = nz / 2, np = capped(I.np, a.np_cap);
     px<T>* dz = buf + np * g.rows;
     cx<T>* twz = reinterpret_cast<cx<T>*>(dz + np * gz.rows);
     cx<T>* tw8 = twz + nz;
@@ -1170,7 +983,7 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline1(StageArgs a
   const cx<T> zero = mk(T(0), T(0));
   PAT_G_ITEMS(a)
   CFft &g = I.gm, &gz = I.gz;
-  const int m = g.L, nz = I.nz, nt = I.nt, np = I.np;
+  const int m = g.L, nz = I.nz, nt = I.nt, np = capped(I.np, a.np_cap);
   px<T>* dz = buf + np * g.rows;
   cx<T>* twz = reinterpret_cast<cx<T>*>(dz + np * gz.rows);
   cx<T>* tw8 = twz + nz;
@@ -1260,6 +1073,18 @@ void count_items(StageArgs& a, Items items) {
 
 int cdiv(int x, int y) { return (x + y - 1) / y; }
 
+template <typename T>
+size_t cut_bytes(const Inst& I, bool data) {
+  return data && I.cut_e ? (size_t)(I.cut_e + 1) * (I.cut_e + 1) * sizeof(T) : 0;
+}
+
+// whether this is the data-side pass of an instance with a cut-off
+bool any_cut(const StageArgs& a, const Inst* h) {
+  bool c = false;
+  for (int i = 0; i < a.n && !a.len_nz; ++i) c = c || h[i].cut_e;
+  return c;
+}
+
 template <typename F>
 size_t max_bytes(int n, F f) {
   size_t mx = 0;
@@ -1267,48 +1092,88 @@ size_t max_bytes(int n, F f) {
   return mx;
 }
 
+// A single instance too small to give every CU an item takes narrower tiles
+// (down to two columns) and fewer pairs per item: its time is the latency of
+// one item (128 line detectors x 256 samples: x1 XX -> XX us).  `items(w)` counts
+// the items at width w.
+template <typename Items>
+int spread_out(int n, int w, int least, Items items) {
+  if (n != 1) return 0;
+  const int full = w;
+  while (w > least && items(w) < num_cu()) w = (w + 1) / 2;
+  return w < full ? w : 0;
+}
+
+// Threads of a transverse pass: one per butterfly of its larger outer stage,
+// at most kBlock.
+int gtr_threads(int n, const GFft& g, int tb) {
+  if (n != 1) return kBlock;
+  const int most = (g.sub0 > g.nbl ? g.sub0 : g.nbl) * tb;
+  return most >= kBlock ? kBlock : (most + 63) / 64 * 64;
+}
+
 }  // namespace
 
 template <typename T>
 hipError_t General<T>::x1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  count_items(a, [&](int i) { return h[i].n2 * cdiv(a.len_nz ? h[i].nz : h[i].nt, 2 * h[i].gtb1); });
-  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gtile(h[i].g1, h[i].gtb1, sizeof(cx<T>)); });
-  return launch_persistent(k_gtr_x1<T>, "dft_x1", a, shm, st, tm);
+  auto tiles = [&](int i, int tb) { return h[i].n2 * cdiv(a.len_nz ? h[i].nz : h[i].nt, 2 * tb); };
+  a.tb_cap = spread_out(a.n, h[0].gtb1, 2, [&](int tb) { return tiles(0, tb); });
+  auto tb = [&](int i) { return capped(h[i].gtb1, a.tb_cap); };
+  count_items(a, [&](int i) { return tiles(i, tb(i)); });
+  const size_t shm =
+      max_bytes(a.n, [&](int i) { return lds_gtile(h[i].g1, tb(i), sizeof(cx<T>)) + cut_bytes<T>(h[i], !a.len_nz); });
+  const int nt = gtr_threads(a.n, h[0].g1, tb(0));
+  if (any_cut(a, h)) return launch_persistent(k_gtr_x1<T, true>, "dft_x1", a, shm, st, tm, nt);
+  return launch_persistent(k_gtr_x1<T, false>, "dft_x1", a, shm, st, tm, nt);
 }
 
 template <typename T>
 hipError_t General<T>::x2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  count_items(a, [&](int i) { return h[i].n2 > 1 ? h[i].h1 * cdiv(a.len_nz ? h[i].nz : h[i].nt, h[i].gtb2) : 0; });
-  const size_t shm = max_bytes(a.n, [&](int i) { return h[i].n2 > 1 ? lds_gtile(h[i].g2, h[i].gtb2, sizeof(cx<T>)) : 0; });
-  return launch_persistent(k_gtr_x2<T>, a.mode ? "idft_x2" : "dft_x2", a, shm, st, tm);
+  auto tiles = [&](int i, int tb) { return h[i].n2 > 1 ? h[i].h1 * cdiv(a.len_nz ? h[i].nz : h[i].nt, tb) : 0; };
+  a.tb_cap = spread_out(a.n, h[0].gtb2, 2, [&](int tb) { return tiles(0, tb); });
+  auto tb = [&](int i) { return capped(h[i].gtb2, a.tb_cap); };
+  count_items(a, [&](int i) { return tiles(i, tb(i)); });
+  const size_t shm = max_bytes(a.n, [&](int i) { return h[i].n2 > 1 ? lds_gtile(h[i].g2, tb(i), sizeof(cx<T>)) : 0; });
+  return launch_persistent(k_gtr_x2<T>, a.mode ? "idft_x2" : "dft_x2", a, shm, st, tm, gtr_threads(a.n, h[0].g2, tb(0)));
 }
 
 template <typename T>
 hipError_t General<T>::c2r(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  count_items(a, [&](int i) { return h[i].n2 * cdiv(a.len_nz ? h[i].nz : h[i].nt, 2 * h[i].gtb1); });
-  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gtile(h[i].g1, h[i].gtb1, sizeof(cx<T>)); });
-  return launch_persistent(k_gtr_c2r<T>, "idft_x1_c2r", a, shm, st, tm);
+  auto tiles = [&](int i, int tb) { return h[i].n2 * cdiv(a.len_nz ? h[i].nz : h[i].nt, 2 * tb); };
+  a.tb_cap = spread_out(a.n, h[0].gtb1, 2, [&](int tb) { return tiles(0, tb); });
+  auto tb = [&](int i) { return capped(h[i].gtb1, a.tb_cap); };
+  count_items(a, [&](int i) { return tiles(i, tb(i)); });
+  const size_t shm =
+      max_bytes(a.n, [&](int i) { return lds_gtile(h[i].g1, tb(i), sizeof(cx<T>)) + cut_bytes<T>(h[i], !a.len_nz); });
+  const int nt = gtr_threads(a.n, h[0].g1, tb(0));
+  if (any_cut(a, h)) return launch_persistent(k_gtr_c2r<T, true>, "idft_x1_c2r", a, shm, st, tm, nt);
+  return launch_persistent(k_gtr_c2r<T, false>, "idft_x1_c2r", a, shm, st, tm, nt);
 }
 
-// Threads of a line kernel: one first-stage butterfly each.
-static int gline_threads(int n, const Inst* h) {
+// Pairs per item, items, LDS and threads (one first-stage butterfly each) of a
+// line kernel.
+static size_t gline_shape(StageArgs& a, const Inst* h, size_t cs, int* threads) {
+  a.np_cap = spread_out(a.n, h[0].np, 1, [&](int np) { return cdiv(h[0].npair, np); });
+  auto np = [&](int i) { return capped(h[i].np, a.np_cap); };
+  count_items(a, [&](int i) { return cdiv(h[i].npair, np(i)); });
   int t = 64;
-  for (int i = 0; i < n; ++i) t = h[i].np * h[i].gm.sub0 > t ? h[i].np * h[i].gm.sub0 : t;
-  return (t + 63) / 64 * 64;
+  for (int i = 0; i < a.n; ++i) t = np(i) * h[i].gm.sub0 > t ? np(i) * h[i].gm.sub0 : t;
+  *threads = (t + 63) / 64 * 64;
+  return max_bytes(a.n, [&](int i) { return lds_gline(h[i], np(i), cs); });
 }
 
 template <typename T>
 hipError_t General<T>::line2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  count_items(a, [&](int i) { return cdiv(h[i].npair, h[i].np); });
-  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gline(h[i], sizeof(cx<T>)); });
-  return launch_persistent(k_gline2<T>, "nufft_fused", a, shm, st, tm, gline_threads(a.n, h));
+  int nt = 0;
+  const size_t shm = gline_shape(a, h, sizeof(cx<T>), &nt);
+  return launch_persistent(k_gline2<T>, "nufft_fused", a, shm, st, tm, nt);
 }
 
 template <typename T>
 hipError_t General<T>::line1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  count_items(a, [&](int i) { return cdiv(h[i].npair, h[i].np); });
-  const size_t shm = max_bytes(a.n, [&](int i) { return lds_gline(h[i], sizeof(cx<T>)); });
-  return launch_persistent(k_gline1<T>, "nufft_adjoint_fused", a, shm, st, tm, gline_threads(a.n, h));
+  int nt = 0;
+  const size_t shm = gline_shape(a, h, sizeof(cx<T>), &nt);
+  return launch_persistent(k_gline1<T>, "nufft_adjoint_fused", a, shm, st, tm, nt);
 }
 
 template struct General<float>;

@@ -1766,17 +1766,32 @@ int num_cu() {
 }
 
 // Workgroups of `block` threads that one CU holds at once for this kernel and
-// LDS size (cached: the query is not free and the answer never changes).
-int resident_blocks(const void* kernel, size_t shmem, int block) {
+// LDS size; 0 and *err on a HIP error.  The first query of a device raises the
+// kernel's dynamic LDS limit where it needs more than 64 KB; both answers are
+// kept (neither call is free on a path that launches in microseconds).
+int resident_blocks(const void* kernel, size_t shmem, int block, hipError_t* err) {
   static std::mutex mu;
-  static std::map<std::tuple<const void*, size_t, int>, int> cache;
+  static std::map<std::tuple<const void*, size_t, int, int>, int> cache;
+  int dev = 0;
+  *err = hipGetDevice(&dev);
+  if (*err != hipSuccess) return 0;
   std::lock_guard<std::mutex> lock(mu);
-  auto it = cache.find({kernel, shmem, block});
+  auto it = cache.find({kernel, shmem, block, dev});
   if (it != cache.end()) return it->second;
+  if (shmem > 65536) {
+    // (the limit only ever rises: another size of the same kernel may be larger)
+    static std::map<std::pair<const void*, int>, size_t> limit;
+    size_t& lim = limit[{kernel, dev}];
+    if (shmem > lim) {
+      *err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+      if (*err != hipSuccess) return 0;
+      lim = shmem;
+    }
+  }
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, shmem) != hipSuccess || per_cu < 1)
     per_cu = 1;
-  cache[{kernel, shmem, block}] = per_cu;
+  cache[{kernel, shmem, block, dev}] = per_cu;
   return per_cu;
 }
 
@@ -1827,6 +1842,7 @@ struct Runner {
     StageArgs a;
     a.n = n;
     a.len_nz = nz ? 1 : 0;
+    a.np_cap = a.tb_cap = 0;
     a.mode = mode;
     a.off[0] = 0;
     for (int i = 0; i < n; ++i) {
@@ -1862,11 +1878,10 @@ struct Runner {
   }
 
   // Whether every instance's transverse passes can run the general-length
-  // kernels (which apply no cut-off: `data` marks the data-side pass), and
-  // every instance's fused line stage.
-  bool gtr_ok(bool data) const {
+  // kernels, and every instance's fused line stage.
+  bool gtr_ok() const {
     for (int i = 0; i < n; ++i)
-      if (!h[i].gtr || (data && h[i].cut_e)) return false;
+      if (!h[i].gtr) return false;
     return true;
   }
   bool gln_ok() const {
@@ -1874,8 +1889,10 @@ struct Runner {
       if (!h[i].gln) return false;
     return true;
   }
-  // (the power-of-two builds keep their own kernels)
-  static bool general(bool ok) { return !P2 && ok; }
+  // The passes before the grid keep their arithmetic with the bf16 grid: a
+  // change of their FP32 rounding (1e-7) moves grid values across bf16 rounding
+  // boundaries and the output by up to 4e-5 of itself.
+  static constexpr bool kBeforeGrid = std::is_same_v<G, bf2>;
 
   template <typename F>
   size_t max_over(F f) const {
@@ -1894,6 +1911,8 @@ struct Runner {
   hipError_t x1(const void* const* in, void* const* out, bool nz) {
     StageArgs a = base(IT_X1, nz, 0, in, out);
     const int len = nz ? h[0].nz : h[0].nt;
+    if (!kBeforeGrid && n == 1 && h[0].gtr && Fixed<T>::takes(h[0].n1, h[0].n2, len)) return Fixed<T>::x1(a, h[0], st, tm);
+    if (!kBeforeGrid && gtr_ok()) return General<T>::x1(a, h, st, tm);
     {
       if (n == 1 && !a.counter && len % 4 == 0 && h[0].tb % 2 == 0 && h[0].n1 * (h[0].tb / 2) <= kPipeU * kBlock) {
         const size_t ew = (size_t)(h[0].cut_e + 1) * (h[0].cut_e + 1);
@@ -1906,18 +1925,19 @@ struct Runner {
           if (L == 256 && tb == pipe_tb<T>(8)) return go(k_tr_x1_pipe<T, RS, 8>);
           if (L == 512 && tb == pipe_tb<T>(9)) return go(k_tr_x1_pipe<T, RS, 9>);
         }
-        if constexpr (sizeof(T) == 4) {
-          if (!general(gtr_ok(!nz))) return go(k_tr_x1_pipe<T, RS>);
-        }
+        if constexpr (sizeof(T) == 4) return go(k_tr_x1_pipe<T, RS>);
       }
     }
-    if (general(gtr_ok(!nz))) return General<T>::x1(a, h, st, tm);
     return launch(k_tr_x1_r2c<T, RS>, "dft_x1", a, max_over([](const Inst& I) { return lds_tile_x1(I, cs); }), st,
                   tm);
   }
   hipError_t x2(void* const* io, bool nz, int inv) {
     StageArgs a = base(IT_X2, nz, inv, io, io);
     const char* name = inv ? "idft_x2" : "dft_x2";
+    const bool before_grid = kBeforeGrid && !inv;
+    if (!before_grid && n == 1 && h[0].gtr && h[0].n2 > 1 && Fixed<T>::takes(h[0].n2, 2 * h[0].h1, nz ? h[0].nz : h[0].nt))
+      return Fixed<T>::x2(a, h[0], st, tm);
+    if (!before_grid && gtr_ok()) return General<T>::x2(a, h, st, tm);
     {
       if (n == 1 && !a.counter && h[0].tb % 2 == 0 && h[0].n2 * (h[0].tb / 2) <= kPipeU * kBlock) {
         const size_t shm = lds_tile_x2(h[0], cs) + (size_t)((h[0].n2 + 3) & ~3) * sizeof(int32_t);
@@ -1928,17 +1948,16 @@ struct Runner {
           if (L == 256 && tb == pipe_tb<T>(8)) return go(k_tr_x2_pipe<T, RS, 8>);
           if (L == 512 && tb == pipe_tb<T>(9)) return go(k_tr_x2_pipe<T, RS, 9>);
         }
-        if constexpr (sizeof(T) == 4) {
-          if (!general(gtr_ok(false))) return go(k_tr_x2_pipe<T, RS>);
-        }
+        if constexpr (sizeof(T) == 4) return go(k_tr_x2_pipe<T, RS>);
       }
     }
-    if (general(gtr_ok(false))) return General<T>::x2(a, h, st, tm);
     return launch(k_tr_x2<T, RS>, name, a, max_over([](const Inst& I) { return lds_tile_x2(I, cs); }), st, tm);
   }
   hipError_t c2r(const void* const* in, void* const* out, bool nz) {
     StageArgs a = base(IT_C2R, nz, 0, in, out);
     const int len = nz ? h[0].nz : h[0].nt;
+    if (n == 1 && h[0].gtr && Fixed<T>::takes(h[0].n1, h[0].n2, len)) return Fixed<T>::c2r(a, h[0], st, tm);
+    if (gtr_ok()) return General<T>::c2r(a, h, st, tm);
     {
       if (n == 1 && !a.counter && !(!nz && h[0].cut_e) && len % 4 == 0 && h[0].tb % 2 == 0 &&
           h[0].n1 * h[0].tb <= 2 * kPipeU * kBlock) {
@@ -1950,12 +1969,9 @@ struct Runner {
           if (L == 256 && tb == pipe_tb<T>(8)) return go(k_tr_c2r_pipe<T, RS, 8>);
           if (L == 512 && tb == pipe_tb<T>(9)) return go(k_tr_c2r_pipe<T, RS, 9>);
         }
-        if constexpr (sizeof(T) == 4) {
-          if (!general(gtr_ok(!nz))) return go(k_tr_c2r_pipe<T, RS>);
-        }
+        if constexpr (sizeof(T) == 4) return go(k_tr_c2r_pipe<T, RS>);
       }
     }
-    if (general(gtr_ok(!nz))) return General<T>::c2r(a, h, st, tm);
     return launch(k_tr_c2r_k1<T, RS>, "idft_x1_c2r", a, max_over([](const Inst& I) { return lds_tile_x1(I, cs); }),
                   st, tm);
   }
@@ -2078,10 +2094,12 @@ struct Runner {
           if (lm == 10) return go(k_line_nufft2_pipe_c<T, TAPS, 10, 9>);
           if (lm == 11) return go(k_line_nufft2_pipe_c<T, TAPS, 11, 10>);
         }
-        if constexpr (sizeof(T) == 4) return go(k_line_nufft2_pipe<T, TAPS>);
+        if constexpr (sizeof(T) == 4) {
+          if (!gln_ok()) return go(k_line_nufft2_pipe<T, TAPS>);
+        }
       }
     }
-    if (general(gln_ok()) && a.pair_ok) return General<T>::line2(a, h, st, tm);
+    if (gln_ok() && a.pair_ok) return General<T>::line2(a, h, st, tm);
     return launch(k_line_nufft2<T, RS, TAPS>, "nufft_fused", a,
                   max_over([](const Inst& I) { return lds_fused2(I, cs); }), st, tm);
   }
@@ -2125,7 +2143,7 @@ struct Runner {
         if (lm == 11) return go(k_line_nufft1_c<T, TAPS, 11, 10>);
       }
     }
-    if (general(gln_ok()) && a.pair_ok) return General<T>::line1(a, h, st, tm);
+    if (gln_ok() && a.pair_ok) return General<T>::line1(a, h, st, tm);
     return launch(k_line_nufft1<T, RS, TAPS>, "nufft_adjoint_fused", a,
                   max_over([](const Inst& I) { return lds_fused1(I, cs); }), st, tm);
   }
@@ -2227,7 +2245,7 @@ hipError_t dispatch_one_build(Op op, int stage, int n, const Inst* h, const Inst
 constexpr int kClasses = 4;
 int radix_class(const Inst& I) {
   if (I.pow2) return 0;
-  if (I.gtr && I.gln && I.fused && !I.cut_e) return 1;
+  if (I.gtr && I.gln && I.fused) return 1;
   return max_radix(1, &I) <= 8 ? 2 : 3;
 }
 

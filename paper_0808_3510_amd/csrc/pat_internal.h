@@ -166,8 +166,8 @@ inline size_t lds_fused1(const Inst& I, size_t cs) {
 // general-length line kernels: np pairs of grid lines and of depth lines
 // (two complex values per point), the depth roots, the 16 roots of the middle
 // grid stage
-inline size_t lds_gline(const Inst& I, size_t cs) {
-  return ((size_t)I.np * (I.gm.rows + I.gz.rows) * 2 + I.nz + 16) * cs;
+inline size_t lds_gline(const Inst& I, int np, size_t cs) {
+  return ((size_t)np * (I.gm.rows + I.gz.rows) * 2 + I.nz + 16) * cs;
 }
 // general-length transverse passes: a tile and the roots
 inline size_t lds_gtile(const GFft& g, int tb, size_t cs) { return ((size_t)g.rows * tb + g.L) * cs; }

@@ -292,7 +292,7 @@ void finish_general(int L, int tw, GFft* g) {
 
 // The internal grid of the general-length line kernels: the smallest 8 r1 rl
 // >= m with r1 a power of two up to 16 and rl one of 8, 10, 12, 14 (steps of
-// at most 1.25 from 64 points on), 0 above 1792 points.
+// at most 1.25 from 64 points on), then 2048, 0 above.
 int general_grid(int m, int* r1, int* rl) {
   for (int a = 1; a <= 16; a *= 2)
     for (int e = 8; e <= 14; e += 2)
@@ -301,18 +301,19 @@ int general_grid(int m, int* r1, int* rl) {
         *rl = e;
         return 8 * a * e;
       }
-  return 0;
+  *r1 = *rl = 16;
+  return m <= 2048 ? 2048 : 0;
 }
 
 // Tile width of a general-length transverse pass: the widest of 32, 16, 8
 // columns whose tile and twiddles stay within 40 KB of LDS (four workgroups
 // per CU), else the widest that fits at all.
-int general_tile(const GFft& g, size_t cs) {
+int general_tile(const GFft& g, size_t cs, size_t cut) {
   auto lds = [&](int tb) { return ((size_t)g.rows * tb + g.L) * cs; };
   for (int tb = 32; tb >= 8; tb /= 2)
     if (lds(tb) <= 40 * 1024) return tb;
   for (int tb = 8; tb >= 1; tb /= 2)
-    if (lds(tb) <= kLdsMax) return tb;
+    if (lds(tb) + cut <= kLdsMax) return tb;
   return 0;
 }
 
@@ -660,11 +661,12 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
   // the general-length kernels (see GFft): 32-bit byte offsets inside an array
   // reach 4 GiB
   const bool small32 = (size_t)I.lines * std::max(g.nt, g.nz) * cs < (size_t(1) << 32);
-  I.gtr = prec != PAT_F32_BF16GRID && small32 && plan_general(n1, I.f1.tw, &I.g1) &&
+  I.gtr = small32 && plan_general(n1, I.f1.tw, &I.g1) &&
           (n2 == 1 || plan_general(n2, I.f2.tw, &I.g2));
   if (I.gtr) {
-    I.gtb1 = general_tile(I.g1, cs);
-    I.gtb2 = n2 == 1 ? 1 : general_tile(I.g2, cs);
+    const size_t cut = I.cut_e ? (size_t)(I.cut_e + 1) * (I.cut_e + 1) * rs : 0;
+    I.gtb1 = general_tile(I.g1, cs, cut);
+    I.gtb2 = n2 == 1 ? 1 : general_tile(I.g2, cs, 0);
     I.gtr = I.gtb1 > 0 && I.gtb2 > 0;
   }
   I.npair = n2 == 1 ? I.h1 : I.lines / 2;
@@ -680,9 +682,9 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
     I.c_g = (double)mg / g.nt;
     // one first-stage butterfly (of a pair) per thread
     I.np = std::max(1, kBlock / I.gm.sub0);
-    while (I.np > 1 && lds_gline(I, cs) > (prec == PAT_F64 ? 80 : 40) * 1024) --I.np;
+    while (I.np > 1 && lds_gline(I, I.np, cs) > (prec == PAT_F64 ? 80 : 40) * 1024) --I.np;
     // (the depth scratch of the type-1 kernel lies in the grid lines)
-    I.gln = lds_gline(I, cs) <= kLdsMax && I.gz.rows <= I.gm.rows ? 1 : 0;
+    I.gln = lds_gline(I, I.np, cs) <= kLdsMax && I.gz.rows <= I.gm.rows ? 1 : 0;
   }
   // workspace: G (lines x nt), grid (lines x m), F (lines x nz)
   const size_t lines = (size_t)I.lines;
