@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpatnufft.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["plan.cpp", "capi.cpp", "general.hip", "transverse.hip", "kernels.hip"]
+SOURCES = ["plan.cpp", "capi.cpp", "general.hip", "linepair.hip", "transverse.hip", "kernels.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions are kept out of the generated code

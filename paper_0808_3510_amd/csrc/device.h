@@ -1012,8 +1012,8 @@ __device__ __forceinline__ void pair_window(double nup, const Inst& I, const Sta
   int j0;
   const double d = tap_origin(I.c * nup, I.ck, &j0);
   const T x = (T)(2.0 * d + 1.0);
-  const bool ongrid = d == -1.0;
   tap_weights_pairs<T, TAPS>(a, x, pw.w);
+  const bool ongrid = d == -1.0;
   pw.on = ongrid;
   const int jm = ongrid ? -(j0 + TAPS - 2) : -(j0 + TAPS - 1);
   pw.jp = wrap_tap<P2>(j0, m, inv_m);
@@ -1200,9 +1200,9 @@ __device__ __forceinline__ void spread_node(const Inst& I, const StageArgs& a, d
     int j0;
     const double d = tap_origin(I.c * nup, I.ck, &j0);
     const T x = (T)(2.0 * d + 1.0);
-    const bool ongrid = d == -1.0;
     T w[TAPS];
     tap_weights_pairs<T, TAPS>(a, x, w);
+    const bool ongrid = d == -1.0;
     const bool rev = neg && !ongrid;
 #pragma unroll
     for (int t = 0; t < TAPS; ++t) wi[P + t] = bitsel(rev, w[TAPS - 1 - t], w[t]);
@@ -1643,9 +1643,9 @@ __device__ __forceinline__ void spread_line_wave(const Inst& I, const StageArgs&
     int j0;
     const double d = tap_origin(I.c * nup, I.ck, &j0);
     const T x = (T)(2.0 * d + 1.0);
-    const bool ongrid = d == -1.0;
     T w[TAPS];
     tap_weights_pairs<T, TAPS>(a, x, w);
+    const bool ongrid = d == -1.0;
     // the weights of -nu+ (w reversed, or w on a grid point), formed only on
     // the paths that hold them
     auto mirror_weights = [&](T* wm) {
@@ -1833,8 +1833,20 @@ int num_cu();
 int resident_blocks(const void* kernel, size_t shmem, int block, hipError_t* err);
 bool launch_faulted();
 
+// One kernel launch over `grid` workgroups of `block` threads.
 template <typename K>
-hipError_t launch(K kernel, const char* name, StageArgs& a, size_t shmem, hipStream_t st, StageTimer* tm) {
+hipError_t launch_grid(K kernel, const char* name, StageArgs& a, size_t shmem, hipStream_t st, StageTimer* tm,
+                       int block, int grid) {
+  if (tm) tm->begin(name, st);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), shmem, st, a);
+  const hipError_t e = hipGetLastError();
+  if (tm) tm->end(st);
+  return e;
+}
+
+template <typename K>
+hipError_t launch(K kernel, const char* name, StageArgs& a, size_t shmem, hipStream_t st, StageTimer* tm,
+                  int block = kBlock) {
   if (a.total <= 0) return hipSuccess;
   if (launch_faulted()) return hipErrorLaunchFailure;
   if (a.counter) {
@@ -1846,16 +1858,11 @@ hipError_t launch(K kernel, const char* name, StageArgs& a, size_t shmem, hipStr
   hipError_t e = hipSuccess;
   int cap = a.total;
   if (a.counter || shmem > 65536) {
-    const int per_cu = resident_blocks(reinterpret_cast<const void*>(kernel), shmem, kBlock, &e);
+    const int per_cu = resident_blocks(reinterpret_cast<const void*>(kernel), shmem, block, &e);
     if (e != hipSuccess) return e;
     if (a.counter) cap = per_cu * num_cu();
   }
-  const int grid = a.total < cap ? a.total : cap;
-  if (tm) tm->begin(name, st);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), shmem, st, a);
-  e = hipGetLastError();
-  if (tm) tm->end(st);
-  return e;
+  return launch_grid(kernel, name, a, shmem, st, tm, block, a.total < cap ? a.total : cap);
 }
 
 // A persistent grid (as many workgroups as fit at once, at most one per item)
@@ -1868,12 +1875,7 @@ hipError_t launch_persistent(K kernel, const char* name, StageArgs& a, size_t sh
   hipError_t e = hipSuccess;
   const int cap = resident_blocks(reinterpret_cast<const void*>(kernel), shmem, block, &e) * num_cu();
   if (e != hipSuccess) return e;
-  const int grid = a.total < cap ? a.total : cap;
-  if (tm) tm->begin(name, st);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), shmem, st, a);
-  e = hipGetLastError();
-  if (tm) tm->end(st);
-  return e;
+  return launch_grid(kernel, name, a, shmem, st, tm, block, a.total < cap ? a.total : cap);
 }
 
 }  // namespace pat

@@ -15,7 +15,7 @@
 // two-stage length crosses LDS once.  The last stage has no twiddles, and the
 // plan puts the large primes there.
 #include "general.h"
-#include "regfft.h"
+#include "linepair.h"
 
 namespace pat {
 
@@ -275,107 +275,8 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_c2r(StageArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Line stages.  A point of a line pair holds both lines' values side by side
-// (one 16-byte LDS access in float), so that the two lines share index
-// arithmetic, twiddles and, for the mirror lines (k1, +-k2) of a 3D plan, the
-// node windows, phases and weights.  2D plans have no mirror lines: a "pair"
-// is one line there, its second half zero.
-
-template <typename T>
-struct alignas(16) px {
-  cx<T> a, b;
-};
-
-// lines and |K_x|^2 terms of pair P
-struct PairLines {
-  int la, lb;     // line indices (lb = -1: none)
-  bool shared;    // the second line has the first one's nodes (or is absent)
-  double ka, kb;  // nu+^2 = k. + b l^2
-};
-__device__ __forceinline__ PairLines pair_lines(CInst& I, int P) {
-  PairLines q;
-  if (I.n2 == 1) {
-    q.la = P;
-    q.lb = -1;
-    q.shared = true;
-    q.ka = q.kb = I.a1 * (double)P * (double)P;
-    return q;
-  }
-  const int h2 = I.n2 >> 1;
-  const int k1 = fdiv(P, I.m_h2), r = P - k1 * h2;
-  q.la = k1 * I.n2 + r;
-  q.lb = k1 * I.n2 + (r ? I.n2 - r : h2);
-  q.shared = r != 0;
-  const double k1t = I.a1 * (double)k1 * (double)k1;
-  q.ka = k1t + I.a2 * (double)r * (double)r;
-  q.kb = r ? q.ka : k1t + I.a2 * (double)h2 * (double)h2;
-  return q;
-}
-
-// line index of one half of pair P (-1: none)
-__device__ __forceinline__ int pair_line(CInst& I, int P, int half) {
-  if (I.n2 == 1) return half ? -1 : P;
-  const int h2 = I.n2 >> 1;
-  const int k1 = fdiv(P, I.m_h2), r = P - k1 * h2;
-  return k1 * I.n2 + (half ? (r ? I.n2 - r : h2) : r);
-}
-
-// DFT of both halves of R pair points
-template <typename T, int R>
-__device__ __forceinline__ void dft_px(px<T>* v) {
-  cx<T> u[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) u[r] = v[r].a;
-  dft_reg<T, R>(u);
-#pragma unroll
-  for (int r = 0; r < R; ++r) v[r].a = u[r];
-#pragma unroll
-  for (int r = 0; r < R; ++r) u[r] = v[r].b;
-  dft_reg<T, R>(u);
-#pragma unroll
-  for (int r = 0; r < R; ++r) v[r].b = u[r];
-}
-template <typename T>
-__device__ __forceinline__ px<T> pmul(px<T> v, cx<T> w) {
-  v.a = cmul(v.a, w);
-  v.b = cmul(v.b, w);
-  return v;
-}
-
-// v[d] *= w^d, d = 1 .. R-1 (a power of two up to 16), powers by a product
-// tree at most four products deep
-template <typename T, int R>
-__device__ __forceinline__ void twiddle_reg(cx<T>* v, cx<T> w1) {
-  cx<T> w[R > 1 ? R : 2];
-  w[1] = w1;
-#pragma unroll
-  for (int d = 2; d < R; ++d) w[d] = (d & (d - 1)) == 0 ? cmul(w[d / 2], w[d / 2]) : cmul(w[d & (d - 1)], w[d & -d]);
-#pragma unroll
-  for (int d = 1; d < R; ++d) v[d] = cmul(v[d], w[d]);
-}
-template <typename T, int R>
-__device__ __forceinline__ void twiddle_px(px<T>* v, cx<T> w1) {
-  cx<T> w[R > 1 ? R : 2];
-  w[1] = w1;
-#pragma unroll
-  for (int d = 2; d < R; ++d) w[d] = (d & (d - 1)) == 0 ? cmul(w[d / 2], w[d / 2]) : cmul(w[d & (d - 1)], w[d & -d]);
-#pragma unroll
-  for (int d = 1; d < R; ++d) v[d] = pmul(v[d], w[d]);
-}
-
-// One butterfly of R pair points, one half after the other (both at once would
-// not fit in registers for the larger radices): get(r, half) reads the inputs,
-// tw(d, X) applies the twiddle of output d, put(r, half, X) receives them.
-template <typename T, int R, typename Get, typename Tw, typename Put>
-__device__ __forceinline__ void bfly_px(Get get, Tw tw, Put put) {
-#pragma unroll 1
-  for (int h = 0; h < 2; ++h) {
-    cx<T> v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = get(r, h);
-    dft_emit<T, R>(v, [&](int d, cx<T> x) { put(d, h, d ? tw(d, x) : x); });
-  }
-}
+// Line stages, on line pairs (linepair.h).  2D plans have no mirror lines: a
+// "pair" is one line there, its second half zero.
 
 // Stages of the grid FFT (r0 = 8, r1 a power of two, rl one of 8, 10, 12,
 // 14, 16) over the np pairs of an item.  Pair p's points sit at p * rows, point i
@@ -533,8 +434,6 @@ __device__ __forceinline__ void depth_last(CFft& g, const px<T>* z, int np, Sink
   });
 }
 
-constexpr int kGTaps = 12;  // taps of the default window (2cK at c = 2, K = 3)
-
 // Sums of one window over both lines of a pair: +nup at up, -nup at un.
 template <typename T, bool REV>
 __device__ __forceinline__ void gpair_sums(const px<T>* up, const px<T>* un, const PairWin<T, kGTaps>& pw, px<T>* sp,
@@ -594,8 +493,8 @@ __device__ __forceinline__ void gpair_window(double nup, double c_g, double ck, 
   pw.ph = phase_mpi<T>(nup);
   int j0;
   const double d = tap_origin(c_g * nup, ck, &j0);
-  pw.on = d == -1.0;
   tap_weights_pairs<T, kGTaps>(a, (T)(2.0 * d + 1.0), pw.w);
+  pw.on = d == -1.0;
   pw.jp = wrap_tap<false>(j0, m, inv_m);
   pw.jn = wrap_tap<false>(pw.on ? -(j0 + kGTaps - 2) : -(j0 + kGTaps - 1), m, inv_m);
 }
@@ -754,220 +653,50 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a
   }
 }
 
-// ---------------------------------------------------------------------------
-// Spreading of a line pair by one wavefront, the transpose of the sums above:
-// spread_line_wave (device.h) for both lines of a pair at once.
-
-// Segmented inclusive sums (see WaveSeg) of both halves of the two passes'
-// values, a step as x += on * (x of the source lane) with on = 0 or 1: one
-// multiply-add beside the move instead of an add and a select.  (A value that
-// is not finite spreads over its line here; the line's FFT does so anyway.)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_0(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, true));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_0(double x) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, true);
-  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, true);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <int BIT, int CTRL, int ROWS, typename T>
-__device__ __forceinline__ void seg_step_px(const WaveSeg& s, px<T>& p, px<T>& m) {
-  if (s.use & BIT) {
-    const T on = (s.on & BIT) ? T(1) : T(0);
-    auto add = [&](T& x) { x = fma(dpp_0<CTRL, ROWS>(x), on, x); };
-    add(p.a.x);
-    add(p.a.y);
-    add(p.b.x);
-    add(p.b.y);
-    add(m.a.x);
-    add(m.a.y);
-    add(m.b.x);
-    add(m.b.y);
-  }
-}
+// Spreading of an item's npi pairs (depth spectra D in natural order, pair stride
+// ds) into their grid lines G (m pair cells, zeroed; pair stride gs).  With more
+// waves than pairs, a pair's batches of 64 node pairs go to several waves: they
+// form their batches' windows side by side and add them to the grid in turn.
 template <typename T>
-__device__ __forceinline__ void seg_sum_px(const WaveSeg& s, px<T>& p, px<T>& m) {
-  if (!s.use) return;
-  seg_step_px<1, 0x111, 0xf>(s, p, m);
-  seg_step_px<2, 0x112, 0xf>(s, p, m);
-  seg_step_px<4, 0x114, 0xf>(s, p, m);
-  seg_step_px<8, 0x118, 0xf>(s, p, m);
-  seg_step_px<16, 0x142, 0xa>(s, p, m);
-  seg_step_px<32, 0x143, 0xc>(s, p, m);
-}
-template <typename T>
-__device__ __forceinline__ void add_px(px<T>* c, px<T> v) {
-  px<T> o = *c;
-  o.a = cadd(o.a, v.a);
-  o.b = cadd(o.b, v.b);
-  *c = o;
-}
-template <typename T>
-__device__ __forceinline__ px<T> scl_px(px<T> v, T w) {
-  return px<T>{cscl(v.a, w), cscl(v.b, w)};
-}
-__device__ __forceinline__ int lane_get(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
-__device__ __forceinline__ float lane_get(float v, int k) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
-}
-__device__ __forceinline__ double lane_get(double v, int k) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, k);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), k);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// One pass of general position: first taps j (monotone over the lanes), cells
-// wrapped, segments that may meet modulo m written one lane at a time.
-template <typename T>
-__device__ __forceinline__ void gspread_pass(px<T>* G, int m, int j, int r, bool act, int nact, px<T> v, const T* w) {
+__device__ __forceinline__ void gspread_item(CInst& I, const StageArgs& a, int P0, int npi, px<T>* G, int gs,
+                                             const px<T>* D, int ds) {
   const int L = (int)(threadIdx.x & 63);
-  const int jf = lane_get(j, 0), jl = lane_get(j, nact - 1);
-  const bool distinct = (jf > jl ? jf - jl : jl - jf) < m;
-  const WaveSeg sg = pass_segments(j, act);
-  const bool wr = act && sg.tail;
-#pragma unroll
-  for (int t = 0; t < kGTaps; ++t) {
-    px<T> s = scl_px(v, w[t]);
-    seg_sum(sg, s.a.x, s.a.y);
-    seg_sum(sg, s.b.x, s.b.y);
-    int c = r + t;
-    c -= c >= m ? m : 0;
-    if (distinct) {
-      if (wr) add_px(G + c, s);
-    } else {
-      for (int k = 0; k < 64; ++k) {
-        if (wr && L == k) add_px(G + c, s);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  }
-}
-
-// |l| = q0 .. nz/2 of the pair's nodes at nu+^2 = ak + b l^2 into the grid lines
-// G (m pair cells, zeroed by the caller), the halves that `ha`, `hb` select.
-// D: the pair's depth spectra in natural order.
-template <typename T>
-__device__ __forceinline__ void gspread_nodes(CInst& I, const StageArgs& a, int mode, double ak, bool ha, bool hb,
-                                              px<T>* G, const px<T>* D) {
-  const int L = (int)(threadIdx.x & 63);
-  const int m = I.gm.L, nz = I.nz, half = nz / 2;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
+  const int m = I.gm.L, half = I.nz / 2, mode = a.mode;
   const int q0 = mode == 0 ? 1 : 0, nq = half - q0 + 1;
-  const double wsc = I.wcoef * I.scale, inv_m = 1.0 / (double)m;
-  const cx<T> zero = mk(T(0), T(0));
+  const double inv_m = 1.0 / (double)m;
+  // waves per pair (uniform over the workgroup: barriers depend on it)
+  const int wpp = nw >= 2 * npi && nq > 64 ? nw / npi : 1;
+  const int i = wave % wpp;
 #pragma unroll 1
-  for (int base = 0; base < nq; base += 64) {
-    const int nact = min(64, nq - base);
-    const bool act = L < nact;
-    const int la = act ? q0 + base + L : q0;
-    const double nup = sqrt_nt(ak + I.b * (double)la * (double)la);
-    const cx<T> ph = phase_mpi<T>(nup);
-    px<T> qp, qm;
-    double cf;
-    if (mode == 0) {
-      const bool nyq = la == half;
-      qp = D[nyq ? half : la];
-      qm = D[nyq ? half : nz - la];
-      cf = wsc * (double)la * rcp_nt(nup) * (nyq ? 0.5 : 1.0);
-    } else {
-      qp = D[la];
-      if (la != 0 && la != half) {
-        const px<T> o = D[nz - la];
-        qp.a = cadd(qp.a, o.a);
-        qp.b = cadd(qp.b, o.b);
-      }
-      qm = qp;
-      cf = 0.5 * I.scale;
-    }
-    // (values are dropped by selection, not by a factor 0: an infinite one
-    // must not leave a NaN in its neighbour's cells)
-    const T cff = (T)cf;
-    const cx<T> pc = cscl(ph, cff), pcc = cconj(pc);
-    px<T> vp{cmul(cconj(qp.a), pc), cmul(cconj(qp.b), pc)};
-    px<T> vm{cmul(cconj(qm.a), pcc), cmul(cconj(qm.b), pcc)};
-    if (!(act && ha)) vp.a = vm.a = zero;
-    if (!(act && hb)) vp.b = vm.b = zero;
-    int j0;
-    const double d = tap_origin(I.c_g * nup, I.ck, &j0);
-    const bool on = d == -1.0;
-    T w[kGTaps];
-    tap_weights_pairs<T, kGTaps>(a, (T)(2.0 * d + 1.0), w);
-    const int jm = on ? -(j0 + kGTaps - 2) : -(j0 + kGTaps - 1);
-    const int rp = wrap_tap<false>(j0, m, inv_m), rm = wrap_tap<false>(jm, m, inv_m);
-    if (nact <= 2) {
-      // a few nodes, one after the other, one tap per lane
-      for (int k = 0; k < nact; ++k) {
-        const bool onk = lane_get((int)on, k) != 0;
-        T wt = T(0), wu = T(0);
-#pragma unroll
-        for (int i = 0; i < kGTaps; ++i) {
-          const T wi = lane_get(w[i], k);
-          wt = L == i ? wi : wt;
-          wu = L == (onk ? i : kGTaps - 1 - i) ? wi : wu;
+  for (int p = wave / wpp; p < npi || (wpp > 1 && p < nw); p += nw) {
+    const bool mine = p < npi;
+    const PairLines q = pair_lines(I, P0 + (mine ? p : 0));
+    const px<T>* Dp = D + (mine ? p : 0) * ds;
+    const int passes = wpp > 1 || !q.shared ? 2 : 1;
+#pragma unroll 1
+    for (int t = 0; t < passes; ++t)
+#pragma unroll 1
+      for (int base0 = 0; base0 < nq; base0 += 64 * wpp) {
+        const int base = base0 + 64 * i, nact = min(64, nq - base);
+        const bool act = L < nact;
+        const int la = act ? q0 + base + L : q0;
+        const double nup = sqrt_nt((t ? q.kb : q.ka) + I.b * (double)la * (double)la);
+        px<T> qp, qm;
+        double cf;
+        node_values<T>(I, mode, la, nup, [&](int l) { return Dp[l]; }, &qp, &qm, &cf);
+        SpreadBatch<T> b =
+            spread_setup<T, 0>(a, I.c_g, I.ck, m, inv_m, nup, cscl(phase_mpi<T>(nup), (T)cf), act, nact, t == 0,
+                               q.shared || t == 1, qp, qm);
+        const bool some = mine && nact > 0 && (t == 0 || !q.shared);
+        // the pair's waves in turn: wave i adds its batch between its i-th and
+        // (i+1)-th barrier of wpp
+        for (int o = 0; o < i; ++o) __syncthreads();
+        if (some) spread_apply<T>(b, m, plane_stride(m), G + p * gs);
+        if (wpp > 1) {
+          for (int o = i; o < wpp; ++o) __syncthreads();
         }
-        px<T> bp{mk(lane_get(vp.a.x, k), lane_get(vp.a.y, k)), mk(lane_get(vp.b.x, k), lane_get(vp.b.y, k))};
-        px<T> bm{mk(lane_get(vm.a.x, k), lane_get(vm.a.y, k)), mk(lane_get(vm.b.x, k), lane_get(vm.b.y, k))};
-        int cp = lane_get(rp, k) + L, cm = lane_get(rm, k) + L;
-        cp -= cp >= m ? m : 0;
-        cm -= cm >= m ? m : 0;
-        if (L < kGTaps) add_px(G + cp, scl_px(bp, wt));
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        if (L < kGTaps) add_px(G + cm, scl_px(bm, wu));
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       }
-      continue;
-    }
-    const bool anyon = __any(act && on);
-    const int jf = lane_get(j0, 0), jl = lane_get(j0, nact - 1);
-    const WaveSeg sg = pass_segments(j0, act);
-    const bool wr = act && sg.tail;
-    const bool flat = !__any(wr && (rp > m - kGTaps || rm > m - kGTaps));
-    if (!anyon && flat && passes_disjoint<kGTaps>(jf, jl, m)) {
-      // both passes in one round loop (see spread_pair_wave)
-      px<T>* gp = G + rp;
-      px<T>* gm = G + rm;
-#pragma unroll
-      for (int t = 0; t < kGTaps; ++t) {
-        px<T> xp = scl_px(vp, w[t]), xm = scl_px(vm, w[kGTaps - 1 - t]);
-        seg_sum_px(sg, xp, xm);
-        if (wr) {
-          px<T> ca = gp[t], cb = gm[t];
-          ca.a = cadd(ca.a, xp.a);
-          ca.b = cadd(ca.b, xp.b);
-          cb.a = cadd(cb.a, xm.a);
-          cb.b = cadd(cb.b, xm.b);
-          gp[t] = ca;
-          gm[t] = cb;
-        }
-        // the next round's reads come after this round's writes
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      }
-    } else if (!anyon && jl - jf < m) {
-      // windows that wrap, or passes that meet: the same loop, the cells
-      // wrapped, the second pass's cells read after the first's are written
-#pragma unroll
-      for (int t = 0; t < kGTaps; ++t) {
-        px<T> xp = scl_px(vp, w[t]), xm = scl_px(vm, w[kGTaps - 1 - t]);
-        seg_sum_px(sg, xp, xm);
-        int cp = rp + t, cm = rm + t;
-        cp -= cp >= m ? m : 0;
-        cm -= cm >= m ? m : 0;
-        if (wr) add_px(G + cp, xp);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        if (wr) add_px(G + cm, xm);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      }
-    } else {
-      T wm[kGTaps];
-#pragma unroll
-      for (int t = 0; t < kGTaps; ++t) wm[t] = bitsel(on, w[t], w[kGTaps - 1 - t]);
-      gspread_pass<T>(G, m, j0, rp, act, nact, vp, w);
-      gspread_pass<T>(G, m, jm, rm, act, nact, vm, wm);
-    }
   }
 }
 
@@ -1006,26 +735,21 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline1(StageArgs a
     const uint32_t o = ((uint32_t)line * (uint32_t)nz + (uint32_t)j) * (uint32_t)sizeof(cx<T>);
     const uint32_t st = (uint32_t)gz.sub0 * (uint32_t)sizeof(cx<T>);
 #pragma unroll
-    for (int r = 0; r < decltype(tag)::v; ++r) v[r] = line >= 0 ? *at_off(in, o + (uint32_t)r * st) : zero;
+    for (int r = 0; r < decltype(tag)::v; ++r) {
+      v[r] = mk(T(0), T(0));
+      if (line >= 0) v[r] = *at_off(in, o + (uint32_t)r * st);
+    }
   });
   depth_mid<T>(gz, zs, twz, npi);
   depth_last<T>(gz, zs, npi, [&](int p, int h, int n) {
-    // (an explicit LDS pointer: captured as a generic one its stores stay flat)
-    typedef __attribute__((address_space(3))) cx<T>* LdsPtr;
-    const LdsPtr D = (LdsPtr)(reinterpret_cast<cx<T>*>(dz + p * gz.rows + n) + h);
+    cx<T>* D = reinterpret_cast<cx<T>*>(dz + p * gz.rows + n) + h;
     const int st = 2 * gz.nbl;
-    return [=](int d, cx<T> v) { stx(D + d * st, v); };
+    return [=](int d, cx<T> v) { D[d * st] = v; };
   });
   __syncthreads();
   for (int e = tid; e < npi * g.rows; e += NT) buf[e] = px<T>{zero, zero};
   __syncthreads();
-  for (int p = tid >> 6; p < npi; p += NT >> 6) {
-    const PairLines q = pair_lines(I, __builtin_amdgcn_readfirstlane(P0 + p));
-    px<T>* G = buf + p * g.rows;
-    const px<T>* D = dz + p * gz.rows;
-    for (int s = 0; s < (q.shared ? 1 : 2); ++s)
-      gspread_nodes<T>(I, a, a.mode, s ? q.kb : q.ka, s == 0, q.shared || s == 1, G, D);
-  }
+  gspread_item<T>(I, a, P0, npi, buf, g.rows, dz, gz.rows);
   __syncthreads();
   {
     // first grid stage: from natural order into the padded rows
@@ -1034,7 +758,7 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline1(StageArgs a
     px<T> v[8];
     if (act) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) v[r] = buf[p0 * g.rows + j0 + r * g.sub0];
+      for (int r = 0; r < 8; ++r) v[r] = buf[p0 * g.rows + plane_cell(j0 + r * g.sub0, plane_stride(m))];
       dft_px<T, 8>(v);
       twiddle_px<T, 8>(v, (static_cast<const cx<T>*>(I.tw) + g.tw)[j0]);
     }
@@ -1094,8 +818,7 @@ size_t max_bytes(int n, F f) {
 
 // A single instance too small to give every CU an item takes narrower tiles
 // (down to two columns) and fewer pairs per item: its time is the latency of
-// one item (128 line detectors x 256 samples: x1 XX -> XX us).  `items(w)` counts
-// the items at width w.
+// one item.  `items(w)` counts the items at width w.
 template <typename Items>
 int spread_out(int n, int w, int least, Items items) {
   if (n != 1) return 0;
@@ -1150,14 +873,19 @@ hipError_t General<T>::c2r(StageArgs& a, const Inst* h, hipStream_t st, StageTim
   return launch_persistent(k_gtr_c2r<T, false>, "idft_x1_c2r", a, shm, st, tm, nt);
 }
 
-// Pairs per item, items, LDS and threads (one first-stage butterfly each) of a
-// line kernel.
-static size_t gline_shape(StageArgs& a, const Inst* h, size_t cs, int* threads) {
+// Pairs per item, items, LDS and threads (at least one first-stage butterfly
+// each) of a line kernel.
+static size_t gline_shape(StageArgs& a, const Inst* h, size_t cs, bool spread, int* threads) {
   a.np_cap = spread_out(a.n, h[0].np, 1, [&](int np) { return cdiv(h[0].npair, np); });
   auto np = [&](int i) { return capped(h[i].np, a.np_cap); };
   count_items(a, [&](int i) { return cdiv(h[i].npair, np(i)); });
   int t = 64;
-  for (int i = 0; i < a.n; ++i) t = np(i) * h[i].gm.sub0 > t ? np(i) * h[i].gm.sub0 : t;
+  for (int i = 0; i < a.n; ++i) {
+    // (spreading: two waves per pair where its nodes make two batches)
+    const int s = spread && h[i].nz > 128 ? 128 * np(i) : 0, f = np(i) * h[i].gm.sub0;
+    t = s > t && s <= kBlock ? s : t;
+    t = f > t ? f : t;
+  }
   *threads = (t + 63) / 64 * 64;
   return max_bytes(a.n, [&](int i) { return lds_gline(h[i], np(i), cs); });
 }
@@ -1165,14 +893,14 @@ static size_t gline_shape(StageArgs& a, const Inst* h, size_t cs, int* threads) 
 template <typename T>
 hipError_t General<T>::line2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
   int nt = 0;
-  const size_t shm = gline_shape(a, h, sizeof(cx<T>), &nt);
+  const size_t shm = gline_shape(a, h, sizeof(cx<T>), false, &nt);
   return launch_persistent(k_gline2<T>, "nufft_fused", a, shm, st, tm, nt);
 }
 
 template <typename T>
 hipError_t General<T>::line1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
   int nt = 0;
-  const size_t shm = gline_shape(a, h, sizeof(cx<T>), &nt);
+  const size_t shm = gline_shape(a, h, sizeof(cx<T>), true, &nt);
   return launch_persistent(k_gline1<T>, "nufft_adjoint_fused", a, shm, st, tm, nt);
 }
 

@@ -1,0 +1,201 @@
+// Type-1 line stages of 3D plans with m = 512 or 1024 grid points and nz = m/4,
+// FP32: one line pair per workgroup, of one wave per batch of 64 node pairs.
+//
+// The two lines of a mirror pair (k1, +-k2) share their nodes: window polynomials,
+// phase, FP64 position and segments are formed once for both, by the waves of the
+// pair side by side, and every LDS access serves both lines.  The batches are then
+// added to the grid in turn.  Of 161 us for 256^3 the FFTs and the memory traffic
+// take 59, the set-up of the nodes 17, and the rounds the rest: read-add-write
+// trips through LDS one after the other, at four waves per SIMD.  One line per wave
+// (k_line_nufft1_w): 174 us, and 40 against 31 for 128^3.  At 64^3 the chip is not
+// filled and the shorter chains of k_line_nufft1_w win (14 against 18.6 us).
+#include "general.h"
+#include "linepair.h"
+
+namespace pat {
+
+// Digits of the grid FFT (m = 8 G1 GL) and the depth FFT (nz = Z0 Z1 ZL), rows as
+// in GFft.
+template <int LM>
+struct PairPlan {
+  static constexpr int m = 1 << LM, nz = m / 4, nt = m / 2, half = nz / 2;
+  static constexpr int G1 = 8, GL = LM == 10 ? 16 : 8;
+  static constexpr int GLP = GL | 1, GB = (G1 * GLP) | 1, GS = G1 * GL, GN = 8 * G1, rows = 8 * GB;
+  static constexpr int Z0 = LM == 10 ? 8 : 4, Z1 = 8, ZL = 4;
+  static constexpr int ZLP = ZL | 1, ZB = (Z1 * ZLP) | 1, ZS = Z1 * ZL, ZN = Z0 * Z1, zrows = Z0 * ZB;
+  static_assert(8 * G1 * GL == m && Z0 * Z1 * ZL == nz && zrows + nz <= rows, "digits");
+  // batches of 64 node pairs, one per wave
+  static constexpr int NB = (half + 63) / 64, NT = 64 * NB;
+  static constexpr int PS = plane_stride(m);
+  static_assert(4 * PS <= rows, "planes");
+  static constexpr int lds = rows * 16;
+};
+
+template <int LM>
+__global__ __launch_bounds__(PairPlan<LM>::NT, 4) void k_pair_nufft1(StageArgs a) {
+  using T = float;
+  using P = PairPlan<LM>;
+  CInst& I = *(CInst*)a.inst[0];
+  constexpr int m = P::m, nz = P::nz, nt = P::nt, half = P::half, NT = P::NT;
+  px<T>* buf = reinterpret_cast<px<T>*>(pat_smem);
+  const cx<T>* twm = static_cast<const cx<T>*>(I.tw) + I.gm.tw;
+  const cx<T>* twz = static_cast<const cx<T>*>(I.tw) + I.gz.tw;
+  const int tid = (int)threadIdx.x;
+  const PairLines q = pair_lines(I, (int)blockIdx.x);
+  const int h = tid & 1;  // line of the pair, where lanes alternate
+  // depth FFTs of both lines (neighbouring lanes), into natural order behind
+  // their scratch
+  {
+    const cx<T>* in = static_cast<const cx<T>*>(a.in[0]) + (size_t)(h ? q.lb : q.la) * nz;
+    cx<T>* z = reinterpret_cast<cx<T>*>(buf) + h;
+#pragma unroll
+    for (int id = tid >> 1; id < P::ZS; id += NT / 2) {
+      cx<T> v[P::Z0];
+#pragma unroll
+      for (int r = 0; r < P::Z0; ++r) v[r] = in[id + r * P::ZS];
+      const cx<T> w = twz[id];
+      dft_reg<T, P::Z0>(v);
+      twiddle_reg<T, P::Z0>(v, w);
+      cx<T>* s = z + 2 * (id + id / P::ZL * (P::ZLP - P::ZL));
+#pragma unroll
+      for (int r = 0; r < P::Z0; ++r) s[2 * r * P::ZB] = v[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int id = tid >> 1; id < P::Z0 * P::ZL; id += NT / 2) {
+      const int blk = id / P::ZL, j = id % P::ZL;
+      cx<T>* s = z + 2 * (blk * P::ZB + j);
+      cx<T> v[P::Z1];
+#pragma unroll
+      for (int r = 0; r < P::Z1; ++r) v[r] = s[2 * r * P::ZLP];
+      dft_reg<T, P::Z1>(v);
+      twiddle_reg<T, P::Z1>(v, twz[j * P::Z0]);
+#pragma unroll
+      for (int r = 0; r < P::Z1; ++r) s[2 * r * P::ZLP] = v[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int id = tid >> 1; id < P::ZN; id += NT / 2) {
+      const int d1 = id % P::Z0, d2 = id / P::Z0;
+      const cx<T>* s = z + 2 * (d1 * P::ZB + d2 * P::ZLP);
+      cx<T> v[P::ZL];
+#pragma unroll
+      for (int r = 0; r < P::ZL; ++r) v[r] = s[2 * r];
+      dft_reg<T, P::ZL>(v);
+      cx<T>* d = z + 2 * (P::zrows + id);
+#pragma unroll
+      for (int r = 0; r < P::ZL; ++r) d[2 * r * P::ZN] = v[r];
+    }
+    __syncthreads();
+  }
+  // each wave takes its batch's node values into registers, then the whole
+  // region becomes the grid
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const px<T>* D = buf + P::zrows;
+  px<T> q0 = D[0];
+  q0 = px<T>{mk(lane_get(q0.a.x, 0), lane_get(q0.a.y, 0)), mk(lane_get(q0.b.x, 0), lane_get(q0.b.y, 0))};
+  constexpr int nact = half < 64 ? half : 64;
+  const bool act = (tid & 63) < nact;
+  const int la = min(64 * wave + (tid & 63) + 1, half);
+  px<T> qp, qm;
+  double cf;
+  node_values<T>(I, 1, la, 0.0, [&](int l) { return D[l]; }, &qp, &qm, &cf);  // (A: cf holds for every node)
+  if (a.mode == 0) {
+    qp = D[la];
+    qm = la == half ? qp : D[nz - la];
+  }
+  __syncthreads();
+  const px<T> zero{mk(T(0), T(0)), mk(T(0), T(0))};
+  for (int e = tid; e < 4 * P::PS; e += NT) buf[e] = zero;
+  // (A's node l = 0 is a pass of its own, of the last wave)
+  const int passes = (q.shared ? 1 : 2) * (a.mode == 0 ? 1 : 2);
+#pragma unroll 1
+  for (int s = 0; s < passes; ++s) {
+    const bool l0 = a.mode != 0 && (s & 1), second = (a.mode == 0 ? s : s >> 1) != 0;
+    const bool some = !l0 || wave == P::NB - 1;
+    const int l = l0 ? 0 : la;
+    const double nup = sqrt_nt((second ? q.kb : q.ka) + I.b * (double)l * (double)l);
+    const double w = a.mode == 0 ? I.wcoef * I.scale * (double)la * rcp_nt(nup) * (la == half ? 0.5 : 1.0) : cf;
+    SpreadBatch<T> b = spread_setup<T, m>(a, 2.0, I.ck, m, 0.0, nup, cscl(phase_mpi<T>(nup), (T)w),
+                                          l0 ? (tid & 63) == 0 : act, l0 ? 1 : nact, !second, q.shared || second,
+                                          l0 ? q0 : qp, l0 ? q0 : qm);
+    // the waves add their batches in turn
+    __syncthreads();
+    for (int o = 0; o < wave; ++o) __syncthreads();
+    if (some) spread_apply<T>(b, m, P::PS, buf);
+    for (int o = wave + 1; o < P::NB; ++o) __syncthreads();
+  }
+  __syncthreads();
+  // grid FFTs: the first stage takes the line from natural order into the
+  // padded rows through registers
+  {
+    constexpr int U = P::GS >= NT ? P::GS / NT : 1;
+    px<T> v[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = tid + NT * u;
+      if (j < P::GS) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[u][r] = buf[plane_cell(j, P::PS) + r * (P::GS / 4)];
+        dft_px<T, 8>(v[u]);
+        twiddle_px<T, 8>(v[u], twm[j]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = tid + NT * u;
+      if (j < P::GS) {
+        px<T>* s = buf + j + j / P::GL * (P::GLP - P::GL);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) s[r * P::GB] = v[u][r];
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll 1
+  for (int id = tid; id < 8 * P::GL; id += NT) {
+    const int blk = id / P::GL, j = id % P::GL;
+    px<T>* s = buf + blk * P::GB + j;
+    px<T> v[P::G1];
+#pragma unroll
+    for (int r = 0; r < P::G1; ++r) v[r] = s[r * P::GLP];
+    dft_px<T, P::G1>(v);
+    twiddle_px<T, P::G1>(v, twm[8 * j]);
+#pragma unroll
+    for (int r = 0; r < P::G1; ++r) s[r * P::GLP] = v[r];
+  }
+  __syncthreads();
+  // last stage, one line per lane: X_n = s_n conj(G_k), k = (n - nt/2) mod m: the
+  // outputs k = n + d GN of the first and the last quarter of d, the others are
+  // not formed
+  const T* sn = static_cast<const T*>(I.sn_g);
+  cx<T>* x = static_cast<cx<T>*>(a.out[0]) + (size_t)(h ? q.lb : q.la) * nt;
+#pragma unroll 1
+  for (int id = tid >> 1; id < P::GN; id += NT / 2) {
+    const cx<T>* s = reinterpret_cast<const cx<T>*>(buf + id % 8 * P::GB + id / 8 * P::GLP) + h;
+    cx<T> v[P::GL];
+#pragma unroll
+    for (int r = 0; r < P::GL; ++r) v[r] = s[2 * r];
+    dft_reg<T, P::GL>(v);
+#pragma unroll
+    for (int d = 0; d < P::GL / 4; ++d) {
+      const int np = id + d * P::GN + nt / 2, nm = id + (d + 3 * P::GL / 4) * P::GN - m + nt / 2;
+      x[np] = cscl(cconj(v[d]), sn[np]);
+      x[nm] = cscl(cconj(v[d + 3 * P::GL / 4]), sn[nm]);
+    }
+  }
+}
+
+bool PairLine::takes(const Inst& h) {
+  return h.gln && h.n2 > 1 && h.m == 2 * h.nt && 4 * h.nz == h.m && (h.m == 512 || h.m == 1024);
+}
+
+hipError_t PairLine::line1(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm) {
+  a.total = h.npair;
+  a.counter = nullptr;
+  if (h.m == 512) return launch(k_pair_nufft1<9>, "nufft_adjoint_fused", a, PairPlan<9>::lds, st, tm, PairPlan<9>::NT);
+  return launch(k_pair_nufft1<10>, "nufft_adjoint_fused", a, PairPlan<10>::lds, st, tm, PairPlan<10>::NT);
+}
+
+}  // namespace pat

@@ -679,6 +679,7 @@ pat_status build_plan(const pat_geometry& gin, pat_plan* p, std::string* err) {
     I.gm.r1 = gr1;
     I.gm.rl = grl;
     finish_general(mg, mg != m ? (int)twg_at : I.fm.tw, &I.gm);
+    I.gm.rows = std::max(I.gm.rows, 4 * plane_stride(mg));
     I.c_g = (double)mg / g.nt;
     // one first-stage butterfly (of a pair) per thread
     I.np = std::max(1, kBlock / I.gm.sub0);

@@ -8,8 +8,7 @@ namespace pat {
 
 // Descriptors are read through the constant address space: their fields then
 // come by scalar loads, once, whatever the kernel stores in between (through a
-// plain pointer they were vector loads, repeated after every barrier: the
-// fused type-2 kernel took 79 instead of XX us at 152 x 136 x 368).
+// plain pointer they were vector loads, repeated after every barrier).
 using CInst = const __attribute__((address_space(4))) Inst;
 using CFft = const __attribute__((address_space(4))) GFft;
 
