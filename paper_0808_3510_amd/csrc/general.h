@@ -30,8 +30,9 @@ struct Fixed {
   static hipError_t c2r(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);
 };
 
-// The fused type-1 line stage of a 3D FP32 instance with m = 512 or 1024 grid
+// The fused type-1 line stage of a 3D instance with m = 512 or 1024 grid
 // points and nz = m/4, one line pair per workgroup (linepair.hip).
+template <typename T>
 struct PairLine {
   static bool takes(const Inst& h);
   static hipError_t line1(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);

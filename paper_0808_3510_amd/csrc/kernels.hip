@@ -2110,10 +2110,8 @@ struct Runner {
       const Inst& I = h[0];
       const int lm = __builtin_ctz((unsigned)I.m), dz = lm - __builtin_ctz((unsigned)I.nz);
       StageArgs a = base(IT_LWAVE, true, mode, in, out);
-      if constexpr (sizeof(T) == 4) {
-        // one 3D instance: its lines in mirror pairs (128^3: 31 us against 40)
-        if (n == 1 && a.pair_ok && PairLine::takes(I)) return PairLine::line1(a, I, st, tm);
-      }
+      // one 3D instance: its lines in mirror pairs (128^3: 31 us against 40)
+      if (n == 1 && a.pair_ok && PairLine<T>::takes(I)) return PairLine<T>::line1(a, I, st, tm);
       if (n == 1 && a.pair_ok && (dz == 1 || dz == 2) && lm >= 8 && lm <= 10) {
         const size_t shm = lds_fused1_wave(I, cs);
         auto go = [&](auto kern) { return launch(kern, "nufft_adjoint_fused", a, shm, st, tm); };

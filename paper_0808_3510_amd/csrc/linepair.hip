@@ -1,5 +1,5 @@
-// Type-1 line stages of 3D plans with m = 512 or 1024 grid points and nz = m/4,
-// FP32: one line pair per workgroup, of one wave per batch of 64 node pairs.
+// Type-1 line stages of 3D plans with m = 512 or 1024 grid points and nz = m/4:
+// one line pair per workgroup, of one wave per batch of 64 node pairs.
 //
 // The two lines of a mirror pair (k1, +-k2) share their nodes: window polynomials,
 // phase, FP64 position and segments are formed once for both, by the waves of the
@@ -8,7 +8,9 @@
 // take 59, the set-up of the nodes 17, and the rounds the rest: read-add-write
 // trips through LDS one after the other, at four waves per SIMD.  One line per wave
 // (k_line_nufft1_w): 174 us, and 40 against 31 for 128^3.  At 64^3 the chip is not
-// filled and the shorter chains of k_line_nufft1_w win (14 against 18.6 us).
+// filled and the shorter chains of k_line_nufft1_w win (14 against 18.6 us).  In
+// FP64 (32 bytes a pair point, two waves per SIMD): 367 us against 412 for 256^3,
+// 57 against 79 for 128^3.
 #include "general.h"
 #include "linepair.h"
 
@@ -28,12 +30,11 @@ struct PairPlan {
   static constexpr int NB = (half + 63) / 64, NT = 64 * NB;
   static constexpr int PS = plane_stride(m);
   static_assert(4 * PS <= rows, "planes");
-  static constexpr int lds = rows * 16;
+  static constexpr int points = rows;
 };
 
-template <int LM>
-__global__ __launch_bounds__(PairPlan<LM>::NT, 4) void k_pair_nufft1(StageArgs a) {
-  using T = float;
+template <typename T, int LM>
+__global__ __launch_bounds__((PairPlan<LM>::NT), (sizeof(T) == 4 ? 4 : 2)) void k_pair_nufft1(StageArgs a) {
   using P = PairPlan<LM>;
   CInst& I = *(CInst*)a.inst[0];
   constexpr int m = P::m, nz = P::nz, nt = P::nt, half = P::half, NT = P::NT;
@@ -187,15 +188,23 @@ __global__ __launch_bounds__(PairPlan<LM>::NT, 4) void k_pair_nufft1(StageArgs a
   }
 }
 
-bool PairLine::takes(const Inst& h) {
+template <typename T>
+bool PairLine<T>::takes(const Inst& h) {
   return h.gln && h.n2 > 1 && h.m == 2 * h.nt && 4 * h.nz == h.m && (h.m == 512 || h.m == 1024);
 }
 
-hipError_t PairLine::line1(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm) {
+template <typename T>
+hipError_t PairLine<T>::line1(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm) {
   a.total = h.npair;
   a.counter = nullptr;
-  if (h.m == 512) return launch(k_pair_nufft1<9>, "nufft_adjoint_fused", a, PairPlan<9>::lds, st, tm, PairPlan<9>::NT);
-  return launch(k_pair_nufft1<10>, "nufft_adjoint_fused", a, PairPlan<10>::lds, st, tm, PairPlan<10>::NT);
+  auto go = [&](auto kern, int points, int threads) {
+    return launch(kern, "nufft_adjoint_fused", a, points * sizeof(px<T>), st, tm, threads);
+  };
+  if (h.m == 512) return go(k_pair_nufft1<T, 9>, PairPlan<9>::points, PairPlan<9>::NT);
+  return go(k_pair_nufft1<T, 10>, PairPlan<10>::points, PairPlan<10>::NT);
 }
+
+template struct PairLine<float>;
+template struct PairLine<double>;
 
 }  // namespace pat
