@@ -36,6 +36,9 @@ template <typename T>
 struct PairLine {
   static bool takes(const Inst& h);
   static hipError_t line1(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);
+  // stand-alone spreading of one 3D instance, the grid in the compute type
+  static bool spreads(const Inst& h);
+  static hipError_t spread(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm);
 };
 
 }  // namespace pat

@@ -2037,6 +2037,16 @@ struct Runner {
                   max_over([](const Inst& I) { return lds_interp(I, cs); }), st, tm);
   }
   hipError_t spread(const void* const* in, void* const* out, int mode) {
+    if constexpr (sizeof(T) == 8 && TAPS == 12) {
+      // one 3D instance with pairs enough for a wave per SIMD and more: its lines
+      // in mirror pairs (256^3: 319 us against 377, 128^3: 48 against 83; 32^3: 17
+      // against 12, left below)
+      if (n == 1 && PairLine<T>::spreads(h[0])) {
+        StageArgs a = base(IT_LINE, true, mode, in, out);
+        if (a.pair_ok) return PairLine<T>::spread(a, h[0], st, tm);
+        next_counter--;  // (the counter taken by base() above is not used)
+      }
+    }
     if constexpr (sizeof(T) == 4 && TAPS > 0 && TAPS % 2 == 0) {
       // FP32 with the paired taps: one line per wavefront (its grid line in
       // LDS, up to 2048 points)

@@ -188,6 +188,73 @@ __global__ __launch_bounds__((PairPlan<LM>::NT), (sizeof(T) == 4 ? 4 : 2)) void 
   }
 }
 
+// Stand-alone spreading of 3D plans (any m that is a multiple of 4, one instance):
+// one line pair per workgroup as above, the grid lines written out conjugated.  In
+// FP64 319 us for 256^3, where the gather (k_line_spread) takes 377 and the writes
+// alone about 90; in FP32 it equals k_line_spread_w there (135 us) and loses below,
+// so only the FP64 one is built.
+template <typename T>
+__global__ __launch_bounds__(kBlock, (sizeof(T) == 4 ? 4 : 2)) void k_pair_spread(StageArgs a) {
+  CInst& I = *(CInst*)a.inst[0];
+  px<T>* buf = reinterpret_cast<px<T>*>(pat_smem);
+  const int NT = blockDim.x, tid = (int)threadIdx.x, L = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = NT >> 6;
+  const int m = I.m, ps = plane_stride(m), nz = I.nz, half = nz / 2;
+  const double inv_m = 1.0 / (double)m;
+  const PairLines q = pair_lines(I, (int)blockIdx.x);
+  const cx<T>* fa = static_cast<const cx<T>*>(a.in[0]) + (size_t)q.la * nz;
+  const cx<T>* fb = static_cast<const cx<T>*>(a.in[0]) + (size_t)q.lb * nz;
+  const px<T> zero{mk(T(0), T(0)), mk(T(0), T(0))};
+  for (int e = tid; e < 4 * ps; e += NT) buf[e] = zero;
+  // turns of nw batches; A's node l = 0 is a turn of its own, of the last wave
+  const int turns = (half + 64 * nw - 1) / (64 * nw) + (a.mode == 0 ? 0 : 1), all = q.shared ? turns : 2 * turns;
+#pragma unroll 1
+  for (int s = 0; s < all; ++s) {
+    const bool second = s >= turns;
+    const int u = second ? s - turns : s;
+    const bool l0 = a.mode != 0 && u == turns - 1;
+    const int base = l0 ? 0 : 64 * (u * nw + wave) + 1;
+    const int nact = l0 ? (wave == nw - 1 ? 1 : 0) : min(64, half + 1 - base);
+    const bool act = L < nact;
+    const int la = l0 ? 0 : act ? base + L : 1;
+    const double nup = sqrt_nt((second ? q.kb : q.ka) + I.b * (double)la * (double)la);
+    px<T> qp, qm;
+    double cf;
+    node_values<T>(I, a.mode, la, nup, [&](int l) { return px<T>{fa[l], fb[l]}; }, &qp, &qm, &cf);
+    const cx<T> ph = I.centred ? phase_mpi<T>(nup) : mk(T(1), T(0));
+    SpreadBatch<T> b = spread_setup<T, 0>(a, I.c, I.ck, m, inv_m, nup, cscl(ph, (T)cf), act, nact, !second,
+                                          q.shared || second, qp, qm);
+    __syncthreads();
+    for (int o = 0; o < wave; ++o) __syncthreads();
+    if (nact > 0) spread_apply<T>(b, m, ps, buf);
+    for (int o = wave + 1; o < nw; ++o) __syncthreads();
+  }
+  __syncthreads();
+  cx<T>* ga = static_cast<cx<T>*>(a.out[0]) + (size_t)q.la * m;
+  cx<T>* gb = static_cast<cx<T>*>(a.out[0]) + (size_t)q.lb * m;
+  for (int j = 2 * tid; j < m; j += 2 * NT) {
+    const px<T> v = buf[plane_cell(j, ps)], w = buf[plane_cell(j + 1, ps)];
+    *reinterpret_cast<px<T>*>(ga + j) = px<T>{cconj(v.a), cconj(w.a)};
+    *reinterpret_cast<px<T>*>(gb + j) = px<T>{cconj(v.b), cconj(w.b)};
+  }
+}
+
+template <typename T>
+bool PairLine<T>::spreads(const Inst& h) {
+  return sizeof(T) == 8 && h.npair >= 8 * num_cu() && h.n2 > 1 && h.m % 4 == 0 && h.m >= 2 * kGTaps && (size_t)h.npair * (h.n2 / 2) < (size_t(1) << 32) &&
+         4 * (size_t)plane_stride(h.m) * sizeof(px<T>) <= 80 * 1024;
+}
+
+template <typename T>
+hipError_t PairLine<T>::spread(StageArgs& a, const Inst& h, hipStream_t st, StageTimer* tm) {
+  a.total = h.npair;
+  a.counter = nullptr;
+  const int nw = (h.nz / 2 + 63) / 64;
+  if constexpr (sizeof(T) == 4) return hipErrorInvalidValue;
+  else
+    return launch(k_pair_spread<T>, "spread", a, 4 * plane_stride(h.m) * sizeof(px<T>), st, tm, 64 * (nw < 4 ? nw : 4));
+}
+
 template <typename T>
 bool PairLine<T>::takes(const Inst& h) {
   return h.gln && h.n2 > 1 && h.m == 2 * h.nt && 4 * h.nz == h.m && (h.m == 512 || h.m == 1024);
