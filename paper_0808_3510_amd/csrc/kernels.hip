@@ -27,15 +27,21 @@
 //                 (k_line_nufft2_pipe: its software pipeline for c = 2;
 //                 k_line_nufft2_pipe_c: the same for sizes fixed at compile
 //                 time; k_line_nufft2_mirror: R on 3D plans with nz = m/4,
-//                 the lines of an item in mirror pairs sharing node windows)
+//                 the lines of an item in mirror pairs sharing node windows,
+//                 for the bf16 grid only the stages after it)
 //   k_line_nufft1 depth DFT + spreading + transposed a2 fused per line in LDS
 //                 (k_line_nufft1_c: sizes fixed at compile time;
 //                 k_line_nufft1_w: one line per wavefront, FP32)
 // The fused kernels never store the oversampled grid; the staged ones do
-// (bf16 grid option, long grid lines, and the stand-alone a3 / spreading
-// entry points).
+// (bf16 grid option where k_line_nufft2_mirror does not apply, long grid lines,
+// and the stand-alone a3 / spreading entry points).
 //
-// Uniform FFTs are in-place decimation-in-frequency mixed-radix transforms in
+// Beside these: transverse.hip (transverse passes of 128, 256 and 512 points),
+// general.hip (transverse passes and line stages of other lengths) and
+// linepair.hip (type-1 line stages of 3D plans by mirror line pairs); Runner
+// chooses.
+//
+// Uniform FFTs here are in-place decimation-in-frequency mixed-radix transforms in
 // LDS; bin k ends at position perm[k] (a table built by the host plan).  Two
 // instantiations exist: radices 2/4/8 with shift arithmetic (all lengths
 // powers of two), and the general one (odd primes up to 23).
@@ -1341,7 +1347,13 @@ static_assert(MirrorLds<float, 10, 256>::TWM == 128 && MirrorLds<float, 10, 256>
 // writes them in natural order over the scratch; the interpolation outputs
 // wait in registers for a barrier and then overwrite the grid as the depth
 // lines.
-template <typename T, int TAPS, int LM, int LZ, int NT>
+//
+// BF: the stages after the grid alone.  The grid lines come from memory, in bf16
+// as k_line_a2_pipe stores them, in place of the grid FFT.  (Rounding the FFT's
+// result in LDS instead took 92 us for all of it, but the compiler contracts
+// the two copies of the FFT differently: bf16 roundings then flip now and then,
+// up to 1.5e-5 of the output's norm, where FP32 rounding leaves 2e-7.)
+template <typename T, int TAPS, int LM, int LZ, int NT, bool BF = false>
 __global__ __launch_bounds__(NT, mirror_waves<T>()) void k_line_nufft2_mirror(StageArgs a) {
   const Inst& I = *a.inst[0];
   constexpr int m = 1 << LM, nt = m / 2, nz = 1 << LZ, NL = 16 * NT / m, half = nz / 2;
@@ -1391,7 +1403,18 @@ __global__ __launch_bounds__(NT, mirror_waves<T>()) void k_line_nufft2_mirror(St
   // arithmetic and the row address run on the scalar unit)
   constexpr bool WU = sub >= 64;
   auto uni = [](int v) { return WU ? __builtin_amdgcn_readfirstlane(v) : v; };
+  uint4 raw[4];  // (BF: four grid values each, points 4 (thread + u NT) ..)
   auto fetch = [&](int item) {
+    if constexpr (BF) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = 4 * ((int)threadIdx.x + u * NT), slot = item * NL + (e >> LM);
+        bool sh;
+        const int row = slot < lines ? mirror_line<true>(I, slot, &sh) : 0;
+        raw[u] = *reinterpret_cast<const uint4*>(static_cast<const bf2*>(a.in[0]) + ((size_t)row << LM) + (e & (m - 1)));
+      }
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int slot = uni(item * NL + bb + u * LPP);
@@ -1412,6 +1435,17 @@ __global__ __launch_bounds__(NT, mirror_waves<T>()) void k_line_nufft2_mirror(St
   for (; item < a.total; item += gridDim.x) {
     const int line0 = item * NL;
     const int nl = min(NL, lines - line0);
+    if constexpr (BF) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = 4 * ((int)threadIdx.x + u * NT);
+        cx<T>* g = buf + (e >> LM) * LS + (e & (m - 1));
+        const uint32_t w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] = mk(bf2f((uint16_t)w[i]), bf2f((uint16_t)(w[i] >> 16)));
+      }
+      if (item + (int)gridDim.x < a.total) fetch(item + gridDim.x);
+    } else {
     // (the deconvolution factors and the first twiddle are read per item, not
     // held across it: the registers go to the later phases)
     T snr[4];
@@ -1458,6 +1492,7 @@ __global__ __launch_bounds__(NT, mirror_waves<T>()) void k_line_nufft2_mirror(St
 #pragma unroll
         for (int r = 0; r < RL; ++r) g[k0 + r * step] = lv[u][r];
       }
+    }
     }
     __syncthreads();
     {
@@ -2061,27 +2096,47 @@ struct Runner {
     return launch(k_line_spread<T, G, TAPS>, "spread", a,
                   max_over([](const Inst& I) { return lds_spread(I, cs); }), st, tm);
   }
+  // R on 3D plans with nz = m/4, m = 2^8 .. 2^11: line groups in mirror pairs
+  bool mirrors(const StageArgs& a, int mode) const {
+    const Inst& I = h[0];
+    return n == 1 && !a.counter && a.pair_ok && mode == 0 && I.m == 2 * I.nt && 4 * I.nz == I.m && I.n2 >= 4 &&
+           I.fm.nst >= 2 && I.fm.rad[0] == 8 && I.m >= 256 && I.m <= 2048;
+  }
+  hipError_t mirror(StageArgs& a) {
+    if constexpr (P2 && TAPS > 0) {
+      constexpr bool BF = sizeof(G) < sizeof(cx<T>);
+      const Inst& I = h[0];
+      // two waves per workgroup up to m = 1024 (one mirror pair there), four at
+      // m = 2048
+      const int nt_ = I.m <= 1024 ? 128 : 256;
+      a.total = cdiv(I.lines, 16 * nt_ / I.m);
+      a.off[1] = a.total;
+      auto go = [&](auto kern, int shm) { return launch_persistent(kern, BF ? "interp_idft_z" : "nufft_fused", a, shm, st, tm, nt_); };
+      if (I.m == 256) return go(k_line_nufft2_mirror<T, TAPS, 8, 6, 128, BF>, MirrorLds<T, 8, 128>::bytes);
+      if (I.m == 512) return go(k_line_nufft2_mirror<T, TAPS, 9, 7, 128, BF>, MirrorLds<T, 9, 128>::bytes);
+      if (I.m == 1024) return go(k_line_nufft2_mirror<T, TAPS, 10, 8, 128, BF>, MirrorLds<T, 10, 128>::bytes);
+      return go(k_line_nufft2_mirror<T, TAPS, 11, 9, 256, BF>, MirrorLds<T, 11, 256>::bytes);
+    }
+    return hipErrorInvalidValue;
+  }
+  // R's interpolation and depth FFT from a stored bf16 grid in one kernel, where
+  // the mirror kernel applies (256^3: 58 us against 55 + 43, 128^3: 16 against 27,
+  // 512^3: 393 against 339 + 383).
+  bool bf_mirror(const void* const* in, void* const* out, int mode, hipError_t* e) {
+    if constexpr (P2 && TAPS > 0 && sizeof(G) < sizeof(cx<T>)) {
+      StageArgs a = base(IT_LF, true, mode, in, out);
+      if (mirrors(a, mode)) {
+        *e = mirror(a);
+        return true;
+      }
+      next_counter--;  // (the counter taken by base() above is not used)
+    }
+    return false;
+  }
   hipError_t nufft2(const void* const* in, void* const* out, int mode) {
     StageArgs a = base(IT_LF, true, mode, in, out);
     if constexpr (P2 && TAPS > 0) {
-      const Inst& I = h[0];
-      if (n == 1 && !a.counter && a.pair_ok && mode == 0 && I.m == 2 * I.nt && 4 * I.nz == I.m && I.n2 >= 4 &&
-          I.fm.nst >= 2 && I.fm.rad[0] == 8) {
-        // R on 3D plans with nz = m/4: line groups in mirror pairs, m = 2^8 .. 2^11
-        const int lm = __builtin_ctz((unsigned)I.m);
-        if (lm >= 8 && lm <= 11) {
-          // two waves per workgroup up to m = 1024 (one mirror pair there),
-          // four at m = 2048
-          const int nt_ = lm <= 10 ? 128 : 256;
-          a.total = cdiv(I.lines, 16 * nt_ / I.m);
-          a.off[1] = a.total;
-          auto go = [&](auto kern, int shm) { return launch_persistent(kern, "nufft_fused", a, shm, st, tm, nt_); };
-          if (lm == 8) return go(k_line_nufft2_mirror<T, TAPS, 8, 6, 128>, MirrorLds<T, 8, 128>::bytes);
-          if (lm == 9) return go(k_line_nufft2_mirror<T, TAPS, 9, 7, 128>, MirrorLds<T, 9, 128>::bytes);
-          if (lm == 10) return go(k_line_nufft2_mirror<T, TAPS, 10, 8, 128>, MirrorLds<T, 10, 128>::bytes);
-          return go(k_line_nufft2_mirror<T, TAPS, 11, 9, 256>, MirrorLds<T, 11, 256>::bytes);
-        }
-      }
+      if (mirrors(a, mode)) return mirror(a);
     }
     if constexpr (P2 && TAPS > 0) {
       // FP32, and FP64 at two waves per SIMD (its launch bound)
@@ -2197,6 +2252,7 @@ hipError_t run_op_t(Op op, int stage, int n, const Inst* h, const Inst* const* d
       if (fwd) {
         if (fused) return r.nufft2(bg, bf, mode);
         PAT_TRY(r.a2(bg, bu));
+        if (hipError_t e = hipSuccess; r.bf_mirror(bu, bf, mode, &e)) return e;
         PAT_TRY(r.interp(bu, bf, mode));
         return r.zfft(bf, 1);
       }

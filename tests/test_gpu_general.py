@@ -103,3 +103,39 @@ def test_batch_of_mixed_lengths_matches_single_calls():
         outs, _ = pat.reconstruct_batched([plans[i] for i in order], [xs[i] for i in order])
         for i, o in zip(order, outs):
             assert torch.equal(o, ref[i]), sizes[i]
+
+
+# (n1, n2, nt, nz): transforms of 128, 256 and 512 points along each axis with
+# rows x length just past the 32 columns per CU from which they run their
+# compile-time kernels (over the time axis: R forward, A^T forward, R^T and A
+# inverse), rows and lengths off the tile sizes
+FIXED = [(128, 66, 130, 20), (256, 34, 250, 16), (512, 18, 462, 12), (66, 128, 132, 18), (30, 256, 270, 16),
+         (14, 512, 600, 12), (128, 128, 66, 66), (256, 6, 1400, 6)]
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("op", OPS)
+@pytest.mark.parametrize("n1,n2,nt,nz", FIXED)
+def test_fixed_transverse_lengths(n1, n2, nt, nz, op, prec):
+    run(op, geo(n1, n2, nt, nz), prec, 1700 + n1)
+
+
+@pytest.mark.parametrize("lm", [8, 9, 10, 11])
+@pytest.mark.parametrize("n2", [4, 8])
+def test_bf16_interpolation_with_depth_fft_matches_staged(lm, n2):
+    """R with the bf16 grid runs interpolation and depth FFT in one kernel for a
+    single 3D plan with nz = m/4, and apart in a batch.  The grid's bits are the same up to
+    values within an FP32 rounding (1e-7 with a margin of 10) of a tie, one in
+    1e-6 / 2^-8 = 3e-4, that move by up to 2^-8: 7e-5 in relative L2.  A grid
+    that is not rounded, or rounded elsewhere, differs by 1e-3."""
+    g = geo(8, n2, 1 << (lm - 1), 1 << (lm - 2))
+    plans = [pat.Plan(g["n1"], n2, g["nt"], g["nz"], g["dx"], g["dt"], g["dz"], g["vs"], precision="bf16grid",
+                      device=DEV) for _ in range(2)]
+    x = torch.from_numpy(inputs.random_array((8, n2, g["nt"]), 1800 + lm)).to(DEV, torch.float32)
+    one = plans[0].reconstruct(x)
+    (a, b), _ = pat.reconstruct_batched(plans, [x, x])
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    rel = ((one - a).double().norm() / a.double().norm()).item()
+    print(f"  m=2^{lm} n2={n2}: {rel:.2e}", flush=True)
+    assert rel <= 7e-5, rel
