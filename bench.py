@@ -102,8 +102,9 @@ def kernel_source_hash():
     """Hash of the kernel sources' code: comments and layout do not count, so
     that recorded counters stay valid across edits that change no kernel."""
     h = hashlib.sha256()
-    for f in ("kernels.hip", "pat_internal.h"):
-        with open(os.path.join(ROOT, "paper_0808_3510_amd", "csrc", f), encoding="utf-8") as fh:
+    src = os.path.join(ROOT, "paper_0808_3510_amd", "csrc")
+    for f in sorted(n for n in os.listdir(src) if n.endswith((".hip", ".h"))):
+        with open(os.path.join(src, f), encoding="utf-8") as fh:
             h.update(code_of(fh.read()).encode())
     return h.hexdigest()[:16]
 
@@ -407,13 +408,15 @@ def oracle_parity(p_np, g, outputs, keep, np):
 KERNEL_OF_STAGE = {
     # library stage name -> kernel symbol prefixes in the profiler's output
     "nufft_fused": ("void pat::k_line_nufft2<", "void pat::k_line_nufft2_pipe<", "void pat::k_line_nufft2_pipe_c<",
-                    "void pat::k_line_nufft2_mirror<"),
-    "nufft_adjoint_fused": ("void pat::k_line_nufft1<", "void pat::k_line_nufft1_c<", "void pat::k_line_nufft1_w<"),
-    "dft_x1": ("void pat::k_tr_x1_r2c<", "void pat::k_tr_x1_pipe<"),
-    "dft_x2": ("void pat::k_tr_x2<", "void pat::k_tr_x2_pipe<"),
-    "idft_x1_c2r": ("void pat::k_tr_c2r_k1<", "void pat::k_tr_c2r_pipe<"),
+                    "void pat::k_line_nufft2_mirror<", "void pat::k_gline2<"),
+    "nufft_adjoint_fused": ("void pat::k_line_nufft1<", "void pat::k_line_nufft1_c<", "void pat::k_line_nufft1_w<",
+                            "void pat::k_pair_nufft1<", "void pat::k_gline1<"),
+    "dft_x1": ("void pat::k_tr_x1_r2c<", "void pat::k_tr_x1_pipe<", "void pat::k_ftr_x1<", "void pat::k_gtr_x1<"),
+    "dft_x2": ("void pat::k_tr_x2<", "void pat::k_tr_x2_pipe<", "void pat::k_ftr_x2<", "void pat::k_gtr_x2<"),
+    "idft_x1_c2r": ("void pat::k_tr_c2r_k1<", "void pat::k_tr_c2r_pipe<", "void pat::k_ftr_c2r<",
+                    "void pat::k_gtr_c2r<"),
     "interp": ("void pat::k_line_interp<", "void pat::k_line_interp_stream<"),
-    "spread": ("void pat::k_line_spread<", "void pat::k_line_spread_w<"),
+    "spread": ("void pat::k_line_spread<", "void pat::k_line_spread_w<", "void pat::k_pair_spread<"),
 }
 
 
