@@ -415,9 +415,19 @@ KERNEL_OF_STAGE = {
     "dft_x2": ("void pat::k_tr_x2<", "void pat::k_tr_x2_pipe<", "void pat::k_ftr_x2<", "void pat::k_gtr_x2<"),
     "idft_x1_c2r": ("void pat::k_tr_c2r_k1<", "void pat::k_tr_c2r_pipe<", "void pat::k_ftr_c2r<",
                     "void pat::k_gtr_c2r<"),
+    "interp_idft_z": ("void pat::k_line_nufft2_mirror<",),
     "interp": ("void pat::k_line_interp<", "void pat::k_line_interp_stream<"),
     "spread": ("void pat::k_line_spread<", "void pat::k_line_spread_w<", "void pat::k_pair_spread<"),
 }
+
+
+def in_stage(name, stage):
+    """Whether kernel symbol ``name`` runs ``stage`` (the mirror kernel's last
+    template argument says whether it starts from a stored bf16 grid)."""
+    if not name.startswith(KERNEL_OF_STAGE[stage]):
+        return False
+    stored = "k_line_nufft2_mirror<" in name and name.split("(")[0].endswith(", true>")
+    return stored == (stage == "interp_idft_z")
 
 
 def traffic_of(stage, workload, precision):
@@ -477,10 +487,10 @@ def traffic_from_counters(fetch_csv, write_csv, copy_bytes, workload, precision,
     # class (the transverse kernels serve R and R^T on lines of nt and of nz
     # samples; their persistent forms launch the same grid for both), and the
     # key carries the group when a stage has several.
-    for stage, prefixes in KERNEL_OF_STAGE.items():
+    for stage in KERNEL_OF_STAGE:
         groups = {}
         for d, (name, grid) in fnames.items():
-            if d not in write or not name.startswith(prefixes):
+            if d not in write or not in_stage(name, stage):
                 continue
             size_class = int(round(math.log2(max(fetch[d], 1.0))))
             groups.setdefault((name, grid, size_class), []).append(d)
@@ -510,8 +520,8 @@ def counters_summary(counter_csvs, trace_csv, workload):
     import csv
 
     def key_of(name):
-        for stage, prefixes in KERNEL_OF_STAGE.items():
-            if name.startswith(prefixes):
+        for stage in KERNEL_OF_STAGE:
+            if in_stage(name, stage):
                 return stage
         return None
 
