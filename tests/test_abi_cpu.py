@@ -141,3 +141,11 @@ def test_long_grid_lines_plan_staged_only(kw):
         pat.pat_plan_set_fused(ptr, False)
     finally:
         pat.pat_plan_destroy(ptr)
+
+
+@pytest.mark.parametrize("device", ["cpu", "cpu:0", "meta"])
+def test_plan_refuses_a_device_that_is_no_gpu(device):
+    """A plan on host memory is refused before its table is uploaded, so that
+    no host pointer ever reaches a kernel."""
+    with pytest.raises(ValueError):
+        pat.Plan(8, 8, 16, 8, device=device)
