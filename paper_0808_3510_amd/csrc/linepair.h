@@ -341,8 +341,15 @@ __device__ __forceinline__ void spread_apply(SpreadBatch<T>& s, int m, int ps, p
   // one by one, one tap per lane (+nu+ on lanes 0 .., -nu+ on lanes 32 ..): a few
   // nodes, values that are not finite (the sums of others stay clear of them;
   // lanes past nact count too: they read a valid node and carry zeros), windows
-  // that may meet at any distance of lanes
-  if (nact <= 2 || __any(!(big - big == T(0))) || jl - jf >= m) {
+  // that may meet at any distance of lanes, nodes that coincide on a grid point
+  // (l^2 lost beside K^2: their edge taps, added after the rounds, share a cell)
+  const bool anyon = __any(s.act && s.on);
+  bool twins = false;
+  if (anyon) {
+    const int key = s.act && s.on ? s.j0 : 0x40000000 + L;
+    twins = __any(__builtin_amdgcn_update_dpp(0, key, 0x138, 0xf, 0xf, true) == key && L > 0);
+  }
+  if (nact <= 2 || twins || __any(!(big - big == T(0))) || jl - jf >= m) {
 #pragma unroll 1
     for (int k = 0; k < nact; ++k) {
       const bool onk = lane_get((int)s.on, k) != 0, minus = L >= 32;
@@ -379,8 +386,9 @@ __device__ __forceinline__ void spread_apply(SpreadBatch<T>& s, int m, int ps, p
   else
     gspread_rounds<T, true, true>(G, ps, m, s.rp, s.rm, wr, s.on, s.vp, s.vm, s.w, sg);
   // the edge taps left out: 12 cells above where w reversed would have them (no
-  // two of the wave's nodes share a first tap there, and they span less than m)
-  if (__any(s.act && s.on)) {
+  // two of the wave's nodes on grid points share a first tap here, and they span
+  // less than m)
+  if (anyon) {
     int c = s.rm + kGTaps;
     c -= c >= m ? m : 0;
     if (s.act && s.on) add_px(G + plane_cell(c, ps), scl_px(s.vm, s.w[kGTaps - 1]));
