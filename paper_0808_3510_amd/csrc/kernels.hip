@@ -1929,6 +1929,33 @@ struct Runner {
   // boundaries and the output by up to 4e-5 of itself.
   static constexpr bool kBeforeGrid = std::is_same_v<G, bf2>;
 
+  // Transverse passes of one instance of powers of two below the Fixed kernels'
+  // threshold that run this file's kernels and not the general-length ones: a
+  // launch of a few workgroups takes the latency of one, and there run-time sizes
+  // cost more than narrower tiles give back.  `pts`: columns of the pass; `pipe`:
+  // the compile-time pipeline applies to it.  Kernel times, these against the
+  // general-length kernels':
+  //   FP32, 128 points, x1 and c2r: 4.2 to 5.4 against 4.9 to 6.6 us up to 4096
+  //     columns, 7.9 against 6.4 at 8192 (x2, and 256 and 512 points: slower at
+  //     every size)
+  //   FP64, 128, 256 and 512 points: 3.9 to 8.8 against 5.8 to 12.2 us up to the
+  //     Fixed kernels' threshold (x2 at 512: even; c2r with a cut-off, which the
+  //     pipeline does not take, gains at 128 only)
+  //   FP64, 64 points and less: 3.9 to 6.4 against 4.0 to 7.1 us up to 4096 columns
+  //     (x2: 1024), slower from there on
+  enum Pass { PASS_X1, PASS_X2, PASS_C2R };
+  bool short_pass(Pass ps, int L, int64_t pts, bool pipe) const {
+    if (RS != 0 || n != 1 || counters) return false;
+    if (sizeof(T) == 4) return L == 128 && ps != PASS_X2 && pipe && pts <= 16 * num_cu();
+    if (L >= 128) return (pipe || (L == 128 && ps == PASS_C2R)) && L <= 512 && !(ps == PASS_X2 && L == 512);
+    return pts <= (ps == PASS_X2 ? 4 : 16) * num_cu();
+  }
+  // whether the plan's tile is the one of the compile-time pipeline of L points
+  bool pipe_length(int L) const {
+    const int ll = L == 128 ? 7 : L == 256 ? 8 : L == 512 ? 9 : 0;
+    return RS == 0 && ll && h[0].tb == pipe_tb<T>(ll);
+  }
+
   template <typename F>
   size_t max_over(F f) const {
     size_t mx = 0;
@@ -1946,10 +1973,12 @@ struct Runner {
   hipError_t x1(const void* const* in, void* const* out, bool nz) {
     StageArgs a = base(IT_X1, nz, 0, in, out);
     const int len = nz ? h[0].nz : h[0].nt;
+    const bool pipe = n == 1 && !a.counter && len % 4 == 0 && h[0].tb % 2 == 0 && h[0].n1 * (h[0].tb / 2) <= kPipeU * kBlock;
     if (!kBeforeGrid && n == 1 && h[0].gtr && Fixed<T>::takes(h[0].n1, h[0].n2, len)) return Fixed<T>::x1(a, h[0], st, tm);
-    if (!kBeforeGrid && gtr_ok()) return General<T>::x1(a, h, st, tm);
+    if (!kBeforeGrid && gtr_ok() && !short_pass(PASS_X1, h[0].n1, (int64_t)h[0].n2 * len, pipe && pipe_length(h[0].n1)))
+      return General<T>::x1(a, h, st, tm);
     {
-      if (n == 1 && !a.counter && len % 4 == 0 && h[0].tb % 2 == 0 && h[0].n1 * (h[0].tb / 2) <= kPipeU * kBlock) {
+      if (pipe) {
         const size_t ew = (size_t)(h[0].cut_e + 1) * (h[0].cut_e + 1);
         const size_t shm = (size_t)h[0].n1 * (h[0].tb + 1) * cs + (size_t)((h[0].n1 + 3) & ~3) * sizeof(int32_t) +
                            (!nz && h[0].cut_e ? 2 * ew * sizeof(T) : 0);
@@ -1972,9 +2001,12 @@ struct Runner {
     const bool before_grid = kBeforeGrid && !inv;
     if (!before_grid && n == 1 && h[0].gtr && h[0].n2 > 1 && Fixed<T>::takes(h[0].n2, 2 * h[0].h1, nz ? h[0].nz : h[0].nt))
       return Fixed<T>::x2(a, h[0], st, tm);
-    if (!before_grid && gtr_ok()) return General<T>::x2(a, h, st, tm);
+    const bool pipe = n == 1 && !a.counter && h[0].tb % 2 == 0 && h[0].n2 * (h[0].tb / 2) <= kPipeU * kBlock;
+    if (!before_grid && gtr_ok() &&
+        !short_pass(PASS_X2, h[0].n2, (int64_t)h[0].h1 * (nz ? h[0].nz : h[0].nt), pipe && pipe_length(h[0].n2)))
+      return General<T>::x2(a, h, st, tm);
     {
-      if (n == 1 && !a.counter && h[0].tb % 2 == 0 && h[0].n2 * (h[0].tb / 2) <= kPipeU * kBlock) {
+      if (pipe) {
         const size_t shm = lds_tile_x2(h[0], cs) + (size_t)((h[0].n2 + 3) & ~3) * sizeof(int32_t);
         auto go = [&](auto kern) { return launch_persistent(kern, name, a, shm, st, tm); };
         if constexpr (RS == 0) {
@@ -1992,10 +2024,12 @@ struct Runner {
     StageArgs a = base(IT_C2R, nz, 0, in, out);
     const int len = nz ? h[0].nz : h[0].nt;
     if (n == 1 && h[0].gtr && Fixed<T>::takes(h[0].n1, h[0].n2, len)) return Fixed<T>::c2r(a, h[0], st, tm);
-    if (gtr_ok()) return General<T>::c2r(a, h, st, tm);
+    const bool pipe = n == 1 && !a.counter && !(!nz && h[0].cut_e) && len % 4 == 0 && h[0].tb % 2 == 0 &&
+                      h[0].n1 * h[0].tb <= 2 * kPipeU * kBlock;
+    if (gtr_ok() && !short_pass(PASS_C2R, h[0].n1, (int64_t)h[0].n2 * len, pipe && pipe_length(h[0].n1)))
+      return General<T>::c2r(a, h, st, tm);
     {
-      if (n == 1 && !a.counter && !(!nz && h[0].cut_e) && len % 4 == 0 && h[0].tb % 2 == 0 &&
-          h[0].n1 * h[0].tb <= 2 * kPipeU * kBlock) {
+      if (pipe) {
         const size_t shm = (size_t)h[0].n1 * (h[0].tb + 1) * cs + (size_t)((h[0].n1 + 3) & ~3) * sizeof(int32_t);
         auto go = [&](auto kern) { return launch_persistent(kern, "idft_x1_c2r", a, shm, st, tm); };
         if constexpr (RS == 0) {

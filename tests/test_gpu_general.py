@@ -139,3 +139,17 @@ def test_bf16_interpolation_with_depth_fft_matches_staged(lm, n2):
     rel = ((one - a).double().norm() / a.double().norm()).item()
     print(f"  m=2^{lm} n2={n2}: {rel:.2e}", flush=True)
     assert rel <= 7e-5, rel
+
+
+# powers of two around the column counts up to which the passes of one small plan run
+# the one-length kernels (4096; FP64 x2 of 64 points and less: 1024), at the tile's
+# smallest sizes, and a length of two samples, which no pipeline takes
+SHORT = [(128, 16, 256, 64), (128, 2, 8, 2), (256, 4, 8, 2), (64, 32, 128, 32), (64, 64, 128, 32), (32, 64, 64, 16),
+         (512, 2, 16, 8), (4, 512, 8, 4), (2, 16, 1024, 8)]
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("op", OPS)
+@pytest.mark.parametrize("n1,n2,nt,nz", SHORT)
+def test_short_transverse_passes(n1, n2, nt, nz, op, prec):
+    run(op, geo(n1, n2, nt, nz), prec, 1900 + n1)
