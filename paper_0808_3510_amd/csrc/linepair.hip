@@ -54,9 +54,8 @@ __global__ __launch_bounds__((PairPlan<LM>::NT), (sizeof(T) == 4 ? 4 : 2)) void 
       cx<T> v[P::Z0];
 #pragma unroll
       for (int r = 0; r < P::Z0; ++r) v[r] = in[id + r * P::ZS];
-      const cx<T> w = twz[id];
       dft_reg<T, P::Z0>(v);
-      twiddle_reg<T, P::Z0>(v, w);
+      twiddle_reg<T, P::Z0>(v, [&](int d) { return twz[id * d]; });
       cx<T>* s = z + 2 * (id + id / P::ZL * (P::ZLP - P::ZL));
 #pragma unroll
       for (int r = 0; r < P::Z0; ++r) s[2 * r * P::ZB] = v[r];
@@ -70,7 +69,7 @@ __global__ __launch_bounds__((PairPlan<LM>::NT), (sizeof(T) == 4 ? 4 : 2)) void 
 #pragma unroll
       for (int r = 0; r < P::Z1; ++r) v[r] = s[2 * r * P::ZLP];
       dft_reg<T, P::Z1>(v);
-      twiddle_reg<T, P::Z1>(v, twz[j * P::Z0]);
+      twiddle_reg<T, P::Z1>(v, [&](int d) { return twz[j * P::Z0 * d]; });
 #pragma unroll
       for (int r = 0; r < P::Z1; ++r) s[2 * r * P::ZLP] = v[r];
     }
@@ -139,7 +138,7 @@ __global__ __launch_bounds__((PairPlan<LM>::NT), (sizeof(T) == 4 ? 4 : 2)) void 
 #pragma unroll
         for (int r = 0; r < 8; ++r) v[u][r] = buf[plane_cell(j, P::PS) + r * (P::GS / 4)];
         dft_px<T, 8>(v[u]);
-        twiddle_px<T, 8>(v[u], twm[j]);
+        twiddle_px<T, 8>(v[u], [&](int d) { return twm[j * d]; });
       }
     }
     __syncthreads();
@@ -162,7 +161,7 @@ __global__ __launch_bounds__((PairPlan<LM>::NT), (sizeof(T) == 4 ? 4 : 2)) void 
 #pragma unroll
     for (int r = 0; r < P::G1; ++r) v[r] = s[r * P::GLP];
     dft_px<T, P::G1>(v);
-    twiddle_px<T, P::G1>(v, twm[8 * j]);
+    twiddle_px<T, P::G1>(v, [&](int d) { return twm[8 * j * d]; });
 #pragma unroll
     for (int r = 0; r < P::G1; ++r) s[r * P::GLP] = v[r];
   }

@@ -153,3 +153,26 @@ SHORT = [(128, 16, 256, 64), (128, 2, 8, 2), (256, 4, 8, 2), (64, 32, 128, 32), 
 @pytest.mark.parametrize("n1,n2,nt,nz", SHORT)
 def test_short_transverse_passes(n1, n2, nt, nz, op, prec):
     run(op, geo(n1, n2, nt, nz), prec, 1900 + n1)
+
+
+# grids of 8 x 16 x 8, 10, 12 and 14 points (the middle radix with the longest powers)
+# and of 8 x 8 x 14; the detectors' step is small, so that the nodes span more than
+# five time windows and the type-1 stage runs the general kernel at any line count
+@pytest.mark.parametrize("op", ["reconstruct", "reconstruct_adjoint"])
+@pytest.mark.parametrize("nt,nz", [(840, 420), (760, 190), (552, 276), (476, 238), (396, 198)])
+def test_fused_lines_are_as_exact_as_staged(nt, nz, op):
+    """The fused line kernels' FP32 error against FP64 is no larger than that of the
+    staged kernels, whose FFTs read every root from the table (both sums over
+    10^5 samples: equal errors differ by a percent; 5 % allowed)."""
+    n1, n2 = 12, 18
+    n_in = nt if op == "reconstruct" else nz
+    kw = dict(dx=1.0 / (1.3 * n1), dt=1.0, dz=nt / nz, vs=1.0, device=DEV)
+    x = torch.from_numpy(inputs.random_array((n1, n2, n_in), 2000 + nt)).to(DEV, torch.float32)
+    exp = getattr(pat.Plan(n1, n2, nt, nz, precision="f64", **kw), op)(x.double())
+    plan = pat.Plan(n1, n2, nt, nz, precision="f32", **kw)
+    err = []
+    for fused in (True, False):
+        plan.set_fused(fused)
+        err.append(((getattr(plan, op)(x).double() - exp).norm() / exp.norm()).item())
+    print(f"  {op} nt={nt} nz={nz}: fused {err[0]:.2e}, staged {err[1]:.2e}", flush=True)
+    assert err[0] <= 1.05 * err[1], err
