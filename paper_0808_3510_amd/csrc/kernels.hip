@@ -2167,6 +2167,35 @@ struct Runner {
     }
     return false;
   }
+  // Type-2 line stages of one instance of powers of two that k_gline2 could take and
+  // that run k_line_nufft2(_pipe): the lengths without a compile-time kernel, as long
+  // as the lines do not fill the chip.  A k_gline2 workgroup carries more pairs and
+  // pays for run-time radices; in 2D half of its pair points are empty.  Kernel
+  // times, these against k_gline2's:
+  //   FP32, 3D: m = 32, 8256 lines 8.3 against 11.8 us, 33024 lines 16.3 against 12.4;
+  //     m = 128, 8256 lines 12.6 against 13.2, 16512 lines 18.1 against 15.7; m = 512,
+  //     nz = 64, 2080 lines 12.5 against 12.8, 4128 lines 16.6 against 13.6; m = 2048,
+  //     nz = 256, 640 lines 14.3 against 15.1, 1032 lines 18.9 against 14.9
+  //   FP32, 2D: 33 to 2049 lines 7.3 to 10.9 against 8.9 to 11.7; m = 1024, nz = 128,
+  //     1025 lines 12.9 against 11.8; m = 2048, 2049 lines 29 against 34
+  //   (m = 128 with nz = 64 only: 11.9 against 10.8)
+  //   FP64, 3D: m = 64, 4352 lines 14.2 against 15.6, 8256 lines 20.2 against 17.0;
+  //     m = 512, nz = 64, 1040 lines 15.9 against 17.3, 2080 lines 25.2 against 19.4;
+  //     m = 2048, nz = 256, 1280 lines 43.5 against 48.9, 2080 lines 67
+  //   FP64, 2D: m up to 64, 11 to 13 against 13 to 15; m = 128 even, from 1500 lines on
+  //     14.9 against 16.2; m = 2048, 257 lines 17.6 against 27.8
+  bool short_type2() const {
+    const Inst& I = h[0];
+    if (RS != 0 || n != 1 || counters || (I.m == 128 && I.nz == 64)) return false;
+    const int64_t pts = (int64_t)I.lines * I.m, cu = num_cu();
+    if (sizeof(T) == 4) {
+      if (I.n2 == 1) return I.m >= 2048 || pts <= 3600 * cu;
+      return pts <= (I.m <= 64 ? 3072 : 4608) * cu;
+    }
+    if (I.n2 == 1) return I.m <= 64 || I.m >= 2048 || (I.m <= 256 && I.lines >= 6 * cu);
+    if (I.m >= 2048) return pts <= 12288 * cu;
+    return I.lines <= 20 * cu && pts <= 2200 * cu;
+  }
   hipError_t nufft2(const void* const* in, void* const* out, int mode) {
     StageArgs a = base(IT_LF, true, mode, in, out);
     if constexpr (P2 && TAPS > 0) {
@@ -2194,11 +2223,11 @@ struct Runner {
           if (lm == 11) return go(k_line_nufft2_pipe_c<T, TAPS, 11, 10>);
         }
         if constexpr (sizeof(T) == 4) {
-          if (!gln_ok()) return go(k_line_nufft2_pipe<T, TAPS>);
+          if (!gln_ok() || short_type2()) return go(k_line_nufft2_pipe<T, TAPS>);
         }
       }
     }
-    if (gln_ok() && a.pair_ok) return General<T>::line2(a, h, st, tm);
+    if (gln_ok() && a.pair_ok && !short_type2()) return General<T>::line2(a, h, st, tm);
     return launch(k_line_nufft2<T, RS, TAPS>, "nufft_fused", a,
                   max_over([](const Inst& I) { return lds_fused2(I, cs); }), st, tm);
   }

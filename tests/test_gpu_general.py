@@ -176,3 +176,17 @@ def test_fused_lines_are_as_exact_as_staged(nt, nz, op):
         err.append(((getattr(plan, op)(x).double() - exp).norm() / exp.norm()).item())
     print(f"  {op} nt={nt} nz={nz}: fused {err[0]:.2e}, staged {err[1]:.2e}", flush=True)
     assert err[0] <= 1.05 * err[1], err
+
+
+# powers of two without compile-time line kernels on both sides of the line counts at
+# which the type-2 stage changes to the general kernel (FP32: m = 512 at 2304 lines,
+# m = 32 at 24576; FP64: 5120 lines, 563200 points; 2D: 1536 lines)
+TYPE2 = [(16, 256, 256, 64), (8, 512, 256, 64), (32, 512, 16, 8), (16, 512, 32, 16), (64, 64, 128, 32),
+         (2048, 1, 128, 32), (4096, 1, 128, 32), (8, 4, 64, 64), (8, 1, 64, 32)]
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("op", ["reconstruct", "forward_adjoint"])
+@pytest.mark.parametrize("n1,n2,nt,nz", TYPE2)
+def test_type2_lines_of_powers_of_two(n1, n2, nt, nz, op, prec):
+    run(op, geo(n1, n2, nt, nz), prec, 2200 + n1)
