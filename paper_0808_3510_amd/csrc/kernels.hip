@@ -2184,9 +2184,12 @@ struct Runner {
   //     m = 2048, nz = 256, 1280 lines 43.5 against 48.9, 2080 lines 67
   //   FP64, 2D: m up to 64, 11 to 13 against 13 to 15; m = 128 even, from 1500 lines on
   //     14.9 against 16.2; m = 2048, 257 lines 17.6 against 27.8
+  // FP64 lines whose general grid is not the plan's (m below 64) stay on it: R^T and A
+  // are transposes of R and A^T to 1e-12 only where both take the same window.
   bool short_type2() const {
     const Inst& I = h[0];
     if (RS != 0 || n != 1 || counters || (I.m == 128 && I.nz == 64)) return false;
+    if (sizeof(T) == 8 && I.gln && I.gm.L != I.m) return false;
     const int64_t pts = (int64_t)I.lines * I.m, cu = num_cu();
     if (sizeof(T) == 4) {
       if (I.n2 == 1) return I.m >= 2048 || pts <= 3600 * cu;

@@ -190,3 +190,33 @@ TYPE2 = [(16, 256, 256, 64), (8, 512, 256, 64), (32, 512, 16, 8), (16, 512, 32, 
 @pytest.mark.parametrize("n1,n2,nt,nz", TYPE2)
 def test_type2_lines_of_powers_of_two(n1, n2, nt, nz, op, prec):
     run(op, geo(n1, n2, nt, nz), prec, 2200 + n1)
+
+
+# grids of their own (m = 16, 32, 140, 600) and the plan's (64, 96, 1024), lines with and
+# without a compile-time kernel, few lines and many
+PAIRS = [(8, 8, 16, 8), (4, 2, 8, 4), (12, 20, 70, 18), (10, 1, 300, 150), (16, 1, 32, 16), (24, 20, 48, 24), (6, 4, 512, 128),
+         (128, 34, 70, 36), (64, 66, 16, 8)]
+
+
+@pytest.mark.parametrize("n1,n2,nt,nz", PAIRS)
+def test_transposes_share_the_window_fp64(n1, n2, nt, nz):
+    """Entries of R and A^T against those of R^T and A, from unit vectors: equal to
+    rounding (1e-14 of the largest, with a margin of 20), where two windows differ by
+    their truncation, some 1e-11.  Both operators of a pair take the same grid
+    whichever kernels they run."""
+    plan = pat.Plan(n1, n2, nt, nz, 1.0, 0.9, 1.1, 1.05, precision="f64", device=DEV)
+
+    def unit(n, i):
+        x = torch.zeros(n1 * n2 * n, dtype=torch.float64, device=DEV)
+        x[i] = 1.0
+        return x.reshape((n1, n2, n) if n2 > 1 else (n1, n))
+
+    for fwd, adj in (("reconstruct", "reconstruct_adjoint"), ("forward_adjoint", "forward")):
+        i = n1 * n2 * nt // 3
+        y = getattr(plan, fwd)(unit(nt, i)).flatten()
+        off = 0.0
+        for j in y.abs().topk(4).indices.tolist() + [n1 * n2 * nz // 2 + 1]:
+            off = max(off, abs(getattr(plan, adj)(unit(nz, j)).flatten()[i].item() - y[j].item()))
+        off /= y.abs().max().item()
+        print(f"  {fwd} {n1}x{n2}x{nt} -> {nz}: {off:.1e}", flush=True)
+        assert off <= 2e-13, off
