@@ -15,6 +15,9 @@ struct General {
   static hipError_t c2r(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm);
   static hipError_t line2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm);
   static hipError_t line1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm);
+  // line1's items of one instance over the workgroups that are resident at once (0 on
+  // a HIP error)
+  static double line1_rounds(const Inst& h);
 };
 
 // The transverse passes of one instance at 128, 256 and 512 points, sizes

@@ -892,35 +892,52 @@ hipError_t General<T>::c2r(StageArgs& a, const Inst* h, hipStream_t st, StageTim
   return launch_persistent(k_gtr_c2r<T, false>, "idft_x1_c2r", a, shm, st, tm, nt);
 }
 
-// Pairs per item, items, LDS and threads (at least one first-stage butterfly
-// each) of a line kernel.
-static size_t gline_shape(StageArgs& a, const Inst* h, size_t cs, bool spread, int* threads) {
-  a.np_cap = spread_out(a.n, h[0].np, 1, [&](int np) { return cdiv(h[0].npair, np); });
-  auto np = [&](int i) { return capped(h[i].np, a.np_cap); };
-  count_items(a, [&](int i) { return cdiv(h[i].npair, np(i)); });
+// Pairs per item (a cap for one instance), LDS and threads (at least one first-stage
+// butterfly each) of a line kernel.
+struct GlineShape {
+  int np_cap, threads;
+  size_t shm;
+};
+static GlineShape gline_shape(int n, const Inst* h, size_t cs, bool spread) {
+  GlineShape g;
+  g.np_cap = spread_out(n, h[0].np, 1, [&](int np) { return cdiv(h[0].npair, np); });
+  auto np = [&](int i) { return capped(h[i].np, g.np_cap); };
   int t = 64;
-  for (int i = 0; i < a.n; ++i) {
+  for (int i = 0; i < n; ++i) {
     // (spreading: two waves per pair where its nodes make two batches)
     const int s = spread && h[i].nz > 128 ? 128 * np(i) : 0, f = np(i) * h[i].gm.sub0;
     t = s > t && s <= kBlock ? s : t;
     t = f > t ? f : t;
   }
-  *threads = (t + 63) / 64 * 64;
-  return max_bytes(a.n, [&](int i) { return lds_gline(h[i], np(i), cs); });
+  g.threads = (t + 63) / 64 * 64;
+  g.shm = max_bytes(n, [&](int i) { return lds_gline(h[i], np(i), cs); });
+  return g;
+}
+static void gline_items(StageArgs& a, const Inst* h, const GlineShape& g) {
+  a.np_cap = g.np_cap;
+  count_items(a, [&](int i) { return cdiv(h[i].npair, capped(h[i].np, g.np_cap)); });
 }
 
 template <typename T>
 hipError_t General<T>::line2(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  int nt = 0;
-  const size_t shm = gline_shape(a, h, sizeof(cx<T>), false, &nt);
-  return launch_persistent(k_gline2<T>, "nufft_fused", a, shm, st, tm, nt);
+  const GlineShape g = gline_shape(a.n, h, sizeof(cx<T>), false);
+  gline_items(a, h, g);
+  return launch_persistent(k_gline2<T>, "nufft_fused", a, g.shm, st, tm, g.threads);
 }
 
 template <typename T>
 hipError_t General<T>::line1(StageArgs& a, const Inst* h, hipStream_t st, StageTimer* tm) {
-  int nt = 0;
-  const size_t shm = gline_shape(a, h, sizeof(cx<T>), true, &nt);
-  return launch_persistent(k_gline1<T>, "nufft_adjoint_fused", a, shm, st, tm, nt);
+  const GlineShape g = gline_shape(a.n, h, sizeof(cx<T>), true);
+  gline_items(a, h, g);
+  return launch_persistent(k_gline1<T>, "nufft_adjoint_fused", a, g.shm, st, tm, g.threads);
+}
+
+template <typename T>
+double General<T>::line1_rounds(const Inst& h) {
+  const GlineShape g = gline_shape(1, &h, sizeof(cx<T>), true);
+  hipError_t e = hipSuccess;
+  const int res = resident_blocks(reinterpret_cast<const void*>(k_gline1<T>), g.shm, g.threads, &e);
+  return e == hipSuccess ? (double)cdiv(h.npair, capped(h.np, g.np_cap)) / (res * num_cu()) : 0.0;
 }
 
 template struct General<float>;

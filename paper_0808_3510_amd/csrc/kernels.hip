@@ -47,6 +47,7 @@
 // powers of two), and the general one (odd primes up to 23).
 #include "device.h"
 
+#include <cmath>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -2234,6 +2235,62 @@ struct Runner {
     return launch(k_line_nufft2<T, RS, TAPS>, "nufft_fused", a,
                   max_over([](const Inst& I) { return lds_fused2(I, cs); }), st, tm);
   }
+  // Type-1 line stages of one instance that k_gline1 could take and that run
+  // k_line_nufft1, one line per workgroup.  Alone on a CU its line takes 14 to 25 us in
+  // FP32 and 16 to 30 in FP64, k_gline1's pair 16 to 45 and 21 to 58 (run-time radices,
+  // the pair's batches in turn; in 2D half a pair is empty), but its gather is walked
+  // once more for every time window that the nodes reach over, and more lines than
+  // workgroups fit at once cost another such time.  So: its rounds over the resident
+  // workgroups (`mine`) against k_gline1's (`theirs`) times the ratio r of the two times
+  // of a round, and the nodes' reach in time windows against a limit.  The line and
+  // both sides, k_line_nufft1's first:
+  //   FP32, 3D, nt = 80: 984 lines 17 against 21 us, 1464 lines 29 against 26; nt = 300:
+  //     504 lines 18 against 26, 1056 lines 30 against 26; nt = nz = 300: 20 against 34 at
+  //     1008 lines; nt = 1000: 504 lines 28 against 36, 732 lines 49 against 40
+  //   FP64, 3D, nt = 80: 732 lines 38 against 39; nt = 300: 252 lines 20 against 36, 528
+  //     lines 35 against 35; nt = 1024 as powers of two: 144 lines 25 against 50, 2112
+  //     lines 185 against 212, 2304 lines 181 against 171
+  //   2D, nt = 300, n1 = 240 (reach 0.94) 17.9 against 19.1 in FP32, n1 = 300 (1.1) 24
+  //     against 20; FP64 21.7 against 27.6 and, n1 = 600 (2.1), 36.7 against 33.7; nt = 1024,
+  //     n1 = 512 in FP64: 48 against 65
+  //   reach, 3D: nt = 20, FP32, n1 = 80 (5.7) 17.6 against 18.6, n1 = 120 (8.5) 21.8 against 18.6
+  //   radices above 8 (nz = 184): 25 to 26 against 24 to 27 in FP32, 2D 31 against 20
+  //   powers of two with several depth lines per workgroup (lpw_a): two against one 17 to
+  //     20 against 18 to 20 (FP64 22 to 25 against 25 to 28), four and eight 25 to 70
+  //     against 16 to 25
+  bool short_type1() const {
+    if constexpr (TAPS > 0) {
+      const Inst& I = h[0];
+      const bool flat = I.n2 == 1, wide = sizeof(T) == 8, two = I.lpw_a == 2;
+      if (n != 1 || counters || (flat ? RS == 23 || I.lpw_a > 1 : I.lpw_a > 2)) return false;
+      if (wide && I.gln && I.gm.L != I.m) return false;  // (see short_type2)
+      hipError_t e = hipSuccess;
+      const int res = resident_blocks(reinterpret_cast<const void*>(k_line_nufft1<T, RS, TAPS>), lds_fused1(I, cs), kBlock, &e);
+      if (e != hipSuccess) return false;
+      const double mine = std::ceil((double)cdiv(I.lines, I.lpw_a) / (res * num_cu()));
+      double theirs = General<T>::line1_rounds(I);
+      const bool full = theirs > 1.0;
+      theirs = full ? std::fmin(theirs + 0.5, std::ceil(theirs)) : 1.0;
+      const double n1h = 0.5 * I.n1, n2h = 0.5 * I.n2, nzh = 0.5 * I.nz;
+      const double reach = std::sqrt(I.a1 * n1h * n1h + I.a2 * n2h * n2h + I.b * nzh * nzh) / I.nt;
+      const bool deep = 2 * I.nz >= I.m;
+      double r, most;
+      if (flat) {
+        r = 1.56;
+        most = wide ? (full ? 5.0 : 2.0) : I.m <= 1024 || deep ? 1.1 : 0.8;
+      } else {
+        if (RS == 23) r = wide ? 1.15 : I.nz > 128 ? 0.95 : 1.3;
+        else if (!wide) r = (deep ? 1.65 : 1.5) * (full ? 0.7 : 1.0);
+        else if (two) r = 1.2;
+        else if (RS == 0 && I.m == 2048 && 4 * I.nz == I.m) r = 1.95;
+        else r = deep ? (full ? 1.9 : 2.0) : 1.6;
+        r *= 1.0 + (full ? 1.3 : 0.4) / I.n2;
+        most = !two ? 7.0 : !wide && I.lines >= 4 * num_cu() ? 1.6 : 0.7;
+      }
+      return (mine > 1.0 ? mine - 0.1 : 1.0) <= r * theirs && reach <= most;
+    }
+    return false;
+  }
   hipError_t nufft1(const void* const* in, void* const* out, int mode) {
     if constexpr (P2 && TAPS > 0 && TAPS % 2 == 0) {
       // one line per wavefront, compile-time sizes for m = 2^8 .. 2^10 and
@@ -2276,7 +2333,7 @@ struct Runner {
         if (lm == 11) return go(k_line_nufft1_c<T, TAPS, 11, 10>);
       }
     }
-    if (gln_ok() && a.pair_ok) return General<T>::line1(a, h, st, tm);
+    if (gln_ok() && a.pair_ok && !short_type1()) return General<T>::line1(a, h, st, tm);
     return launch(k_line_nufft1<T, RS, TAPS>, "nufft_adjoint_fused", a,
                   max_over([](const Inst& I) { return lds_fused1(I, cs); }), st, tm);
   }

@@ -220,3 +220,17 @@ def test_transposes_share_the_window_fp64(n1, n2, nt, nz):
         off /= y.abs().max().item()
         print(f"  {fwd} {n1}x{n2}x{nt} -> {nz}: {off:.1e}", flush=True)
         assert off <= 2e-13, off
+
+
+# type-1 lines whose nodes reach over nine time windows (a small detector step), which
+# the general kernel takes at any number of lines: every length and grid above, and
+# depth lines longer than the time lines
+FAR = [(6, 10, nt, nz) for nt, nz in TIMES] + [(10, 1, nt, nz) for nt, nz in TIMES[::3]] + LENGTHS + \
+      [(6, 6, 46, 64), (6, 6, 20, 30), (6, 6, 300, 300)]
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("op", ["reconstruct_adjoint", "forward"])
+@pytest.mark.parametrize("n1,n2,nt,nz", FAR)
+def test_type1_lines_of_far_nodes(n1, n2, nt, nz, op, prec):
+    run(op, dict(geo(n1, n2, nt, nz), dx=0.05), prec, 2300 + n1 + nt)
