@@ -7,8 +7,8 @@
 // added to the grid in turn.  Of 161 us for 256^3 the FFTs and the memory traffic
 // take 59, the set-up of the nodes 17, and the rounds the rest: read-add-write
 // trips through LDS one after the other, at four waves per SIMD.  One line per wave
-// (k_line_nufft1_w): 174 us, and 40 against 31 for 128^3.  At 64^3 the chip is not
-// filled and the shorter chains of k_line_nufft1_w win (14 against 18.6 us).  In
+// (k_line_nufft1_w): 174 us, and 40 against 31 for 128^3.  Where the chip is not filled
+// the shorter chains of k_line_nufft1_w win (64^3: 14 against 18.6 us; see takes).  In
 // FP64 (32 bytes a pair point, two waves per SIMD): 367 us against 412 for 256^3,
 // 57 against 79 for 128^3.
 #include "general.h"
@@ -254,9 +254,19 @@ hipError_t PairLine<T>::spread(StageArgs& a, const Inst& h, hipStream_t st, Stag
     return launch(k_pair_spread<T>, "spread", a, 4 * plane_stride(h.m) * sizeof(px<T>), st, tm, 64 * (nw < 4 ? nw : 4));
 }
 
+// From 4.5 pairs per CU on in FP32; in FP64, where a pair's latency is longer, from 2.1
+// (m = 512) and 8.2 (m = 1024) on, and with 128 lines k2 or more at any number (the pair
+// r = 0, which takes two passes, is then one in 64).  k_line_nufft1_w below, its time
+// first: FP32, m = 512: 20 to 2300 lines 13 to 17 against 13 to 19 us, 4200 lines 28
+// against 22; m = 1024: 1040 lines 21 against 23, 2300 lines 26 against 26, 4224 lines 40
+// against 36.  FP64, m = 512: 516 lines 21 against 25, 2064 lines 36 against 30; m = 1024:
+// 1032 lines 32 against 37, 4128 lines 73 against 84; with n2 = 128, 640 lines 19 against 17.
 template <typename T>
 bool PairLine<T>::takes(const Inst& h) {
-  return h.gln && h.n2 > 1 && h.m == 2 * h.nt && 4 * h.nz == h.m && (h.m == 512 || h.m == 1024);
+  if (!h.gln || h.n2 == 1 || h.m != 2 * h.nt || 4 * h.nz != h.m || (h.m != 512 && h.m != 1024)) return false;
+  const int cu = num_cu();
+  if (sizeof(T) == 4) return 2 * h.npair > 9 * cu;
+  return h.n2 >= 128 || 10 * h.npair > (h.m == 512 ? 21 : 82) * cu;
 }
 
 template <typename T>

@@ -1,11 +1,14 @@
-"""Stand-alone FP64 spreading by mirror line pairs (3D plans with at least eight
+"""Type-1 line stages by mirror line pairs.  The fused ones of a 3D plan against the
+oracle on sampled lines; stand-alone FP64 spreading (3D plans with at least eight
 line pairs per CU) against the interpolation, line by line: with the same kernel
 weights <N U, V> = <U, N^H V> on every line, up to the rounding of sums of
 nz x 12 products (1e-13 of the norms' product, with a margin of 10)."""
+import numpy as np
 import pytest
 import torch
 
-from paper_0808_3510_amd import pat
+from oracle import recon
+from paper_0808_3510_amd import inputs, pat
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -34,3 +37,31 @@ def test_coinciding_nodes_on_grid_points(n1, n2):
     centre."""
     plan = pat.Plan(n1, n2, 32, 18, 32.0 / n1, 1.0, 2.0 ** 30, 1.0, alpha=3.2, precision="f64", device=DEV)
     check_adjoint(plan, 2100)
+
+
+# more than 4.5 line pairs per CU (FP32) or 128 lines k2 (FP64): m = 512 and 1024
+FUSED = [("f32", 64, 128, 256, 128), ("f32", 128, 64, 512, 256), ("f64", 8, 128, 256, 128), ("f64", 8, 128, 512, 256)]
+
+
+@pytest.mark.parametrize("op", ["reconstruct_adjoint", "forward"])
+@pytest.mark.parametrize("prec,n1,n2,nt,nz", FUSED)
+def test_fused_pairs_match_oracle(prec, n1, n2, nt, nz, op):
+    """The unshared pairs (k2 = 0 with n2/2), mirror pairs and the highest |K|; FP32
+    1e-5, FP64 1e-9 (the window's truncation, with a margin)."""
+    g = dict(n1=n1, n2=n2, nt=nt, nz=nz, dx=1.0, dt=0.9, dz=1.1, vs=1.05)
+    x = inputs.random_array((n1, n2, nz), 2600 + n1)
+    plan = pat.Plan(n1, n2, nt, nz, g["dx"], g["dt"], g["dz"], g["vs"], precision=prec, device=DEV)
+    y = getattr(plan, op)(torch.from_numpy(x).to(DEV, plan.dtype))
+    torch.cuda.synchronize()
+    Y = np.fft.fft2(y.cpu().double().numpy(), axes=(0, 1))
+    lines = [(0, 0), (0, n2 // 2), (1, 0), (n1 // 2, 0), (n1 // 2, n2 // 2), (2, 1), (2, -1), (n1 // 2 - 1, n2 // 2 - 1),
+             (n1 // 2 - 1, 1 - n2 // 2), (1, n2 // 4)]
+    oracle = recon.adjoint_lines if op == "reconstruct_adjoint" else recon.forward_lines
+    X = oracle(x, g, lines)
+    Xm = oracle(x, g, [(-a, -b) for a, b in lines])
+    worst = 0.0
+    for i, (a, b) in enumerate(lines):
+        exp = 0.5 * (X[i] + np.conj(Xm[i]))
+        worst = max(worst, np.linalg.norm(Y[a % n1, b % n2] - exp) / np.linalg.norm(exp))
+    print(f"  {op} {prec} {g}: {worst:.2e}", flush=True)
+    assert worst <= {"f32": 1e-5, "f64": 1e-9}[prec], worst
