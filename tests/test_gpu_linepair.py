@@ -65,3 +65,33 @@ def test_fused_pairs_match_oracle(prec, n1, n2, nt, nz, op):
         worst = max(worst, np.linalg.norm(Y[a % n1, b % n2] - exp) / np.linalg.norm(exp))
     print(f"  {op} {prec} {g}: {worst:.2e}", flush=True)
     assert worst <= {"f32": 1e-5, "f64": 1e-9}[prec], worst
+
+
+# 2048 line pairs and more: depth lines of one batch, of a batch and one node, of two
+# turns with a ragged last one, grids that are no power of two, the longest grid line
+# that fits, and other windows of 12 taps
+SPREAD = [(128, 66, 32, 18, 2.0, 3.0), (128, 66, 260, 130, 2.0, 3.0), (256, 34, 540, 540, 2.0, 3.0), (256, 34, 22, 10, 2.0, 3.0),
+          (128, 66, 1260, 16, 2.0, 3.0), (64, 128, 128, 128, 2.0, 3.0), (128, 66, 40, 30, 3.0, 2.0), (128, 66, 48, 2, 1.5, 4.0)]
+
+
+@pytest.mark.parametrize("n1,n2,nt,nz,c,K", SPREAD)
+def test_spreading_by_pairs_is_adjoint_of_interpolation(n1, n2, nt, nz, c, K):
+    plan = pat.Plan(n1, n2, nt, nz, 1.0, 0.9, 1.1, 1.05, c=c, K=K, precision="f64", device=DEV)
+    check_adjoint(plan, 2700 + nz)
+
+
+@pytest.mark.parametrize("op", ["reconstruct_adjoint", "forward"])
+@pytest.mark.parametrize("n1,n2,nt,nz", [(128, 66, 32, 18), (128, 66, 260, 130), (256, 34, 540, 540)])
+def test_staged_pairs_match_fused_fp64(n1, n2, nt, nz, op):
+    """The staged operators spread by pairs (A with its node l = 0 in a turn of its
+    own), the fused ones do not: equal up to the windows' truncation (1e-11, with a
+    margin of 100)."""
+    plan = pat.Plan(n1, n2, nt, nz, 1.0, 0.9, 1.1, 1.05, precision="f64", device=DEV)
+    x = torch.from_numpy(inputs.random_array((n1, n2, nz), 2800 + nz)).to(DEV)
+    a = getattr(plan, op)(x).clone()
+    plan.set_fused(False)
+    b = getattr(plan, op)(x)
+    rel = ((a - b).norm() / b.norm()).item()
+    mx = ((a - b).abs().max() / b.abs().max()).item()
+    print(f"  {op} {n1}x{n2}x{nt} -> {nz}: relL2 {rel:.1e}, max {mx:.1e}", flush=True)
+    assert rel <= 1e-9 and mx <= 1e-9, (rel, mx)
