@@ -2108,9 +2108,8 @@ struct Runner {
   }
   hipError_t spread(const void* const* in, void* const* out, int mode) {
     if constexpr (sizeof(T) == 8 && TAPS == 12) {
-      // one 3D instance with pairs enough for a wave per SIMD and more: its lines
-      // in mirror pairs (256^3: 319 us against 377, 128^3: 48 against 83; 32^3: 17
-      // against 12, left below)
+      // one 3D instance with pairs enough: its lines in mirror pairs (256^3: 319 us
+      // against 377, 128^3: 48 against 83; see spreads)
       if (n == 1 && PairLine<T>::spreads(h[0])) {
         StageArgs a = base(IT_LINE, true, mode, in, out);
         if (a.pair_ok) return PairLine<T>::spread(a, h[0], st, tm);

@@ -238,10 +238,26 @@ __global__ __launch_bounds__(kBlock, (sizeof(T) == 4 ? 4 : 2)) void k_pair_sprea
   }
 }
 
+// FP64 only, from 8 pairs per CU on (32^3: 17 us against 12 of k_line_spread, 96^3: 31
+// against 50), where a pair's wave or waves find enough others beside them.  Times
+// against k_line_spread's, first the pairs':
+//   one batch per line (nz up to 128): m = 400 to 1600 23 to 49 against 39 to 51 us at 2112
+//     pairs; m = 1800 58 against 53 (nz = 64), 64 against 53 (nz = 128); nz = 16 at any m
+//     (m = 2520: 59 against 83)
+//   several (nz up to 500), whose turns wait for each other: m = 600, nz = 150: 53 against
+//     42 at 2112 pairs, 88 against 87 at 4160; m = 736: 93 against 108 at 5236, 137 against
+//     181 at 8556; m = 1024, nz = 256: 97 against 84 at 4160, 319 against 377 at 16512; m =
+//     1600: 242 against 249 at 10100; m = 2000: 328 against 244 at 8320
+//   nz from 500 on, where k_line_spread's node lists leave two workgroups per CU: 129 against
+//     141 at m = 2000, 155 against 190 at m = 2400
 template <typename T>
 bool PairLine<T>::spreads(const Inst& h) {
-  return sizeof(T) == 8 && h.npair >= 8 * num_cu() && h.n2 > 1 && h.m % 4 == 0 && h.m >= 2 * kGTaps && (size_t)h.npair * (h.n2 / 2) < (size_t(1) << 32) &&
-         4 * (size_t)plane_stride(h.m) * sizeof(px<T>) <= 80 * 1024;
+  const int cu = num_cu();
+  if (sizeof(T) != 8 || h.n2 == 1 || h.npair < 8 * cu || h.m % 4 != 0 || h.m < 2 * kGTaps) return false;
+  if ((size_t)h.npair * (h.n2 / 2) >= (size_t(1) << 32) || 4 * (size_t)plane_stride(h.m) * sizeof(px<T>) > 80 * 1024) return false;
+  if (h.nz <= 32 || h.nz >= 500) return true;
+  if (h.nz <= 128) return h.m <= 1600;
+  return h.npair >= 32 * cu ? h.m <= 1600 : h.npair >= 16 * cu && h.m <= 800;
 }
 
 template <typename T>

@@ -67,10 +67,10 @@ def test_fused_pairs_match_oracle(prec, n1, n2, nt, nz, op):
     assert worst <= {"f32": 1e-5, "f64": 1e-9}[prec], worst
 
 
-# 2048 line pairs and more: depth lines of one batch, of a batch and one node, of two
-# turns with a ragged last one, grids that are no power of two, the longest grid line
-# that fits, and other windows of 12 taps
-SPREAD = [(128, 66, 32, 18, 2.0, 3.0), (128, 66, 260, 130, 2.0, 3.0), (256, 34, 540, 540, 2.0, 3.0), (256, 34, 22, 10, 2.0, 3.0),
+# 2048 line pairs and more (4096 with several batches): depth lines of one batch, of a
+# batch and one node, of two turns with a ragged last one, grids that are no power of
+# two, the longest grid line that fits, and other windows of 12 taps
+SPREAD = [(128, 66, 32, 18, 2.0, 3.0), (128, 128, 260, 130, 2.0, 3.0), (256, 34, 540, 540, 2.0, 3.0), (256, 34, 22, 10, 2.0, 3.0),
           (128, 66, 1260, 16, 2.0, 3.0), (64, 128, 128, 128, 2.0, 3.0), (128, 66, 40, 30, 3.0, 2.0), (128, 66, 48, 2, 1.5, 4.0)]
 
 
@@ -81,7 +81,7 @@ def test_spreading_by_pairs_is_adjoint_of_interpolation(n1, n2, nt, nz, c, K):
 
 
 @pytest.mark.parametrize("op", ["reconstruct_adjoint", "forward"])
-@pytest.mark.parametrize("n1,n2,nt,nz", [(128, 66, 32, 18), (128, 66, 260, 130), (256, 34, 540, 540)])
+@pytest.mark.parametrize("n1,n2,nt,nz", [(128, 66, 32, 18), (128, 128, 260, 130), (256, 34, 540, 540)])
 def test_staged_pairs_match_fused_fp64(n1, n2, nt, nz, op):
     """The staged operators spread by pairs (A with its node l = 0 in a turn of its
     own), the fused ones do not: equal up to the windows' truncation (1e-11, with a
