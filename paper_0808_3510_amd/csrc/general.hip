@@ -719,10 +719,11 @@ __device__ __forceinline__ void gspread_item(CInst& I, const StageArgs& a, int P
 }
 
 // R^T and A: per item np line pairs.  Their depth DFTs read the spectra from
-// memory and leave them in natural order in LDS; each wavefront spreads whole
-// pairs into their grid lines (no block barrier inside); the grid DFTs of all
-// pairs run together and the last stage writes the picked, deconvolved
-// samples X_n = s_n conj(G_k), k = (n - nt/2) mod m, to memory.
+// memory and leave them in natural order in LDS; wavefronts spread the pairs into
+// their grid lines, one each or, where a pair's nodes make two batches, several per
+// pair that add theirs in turn (gspread_item); the grid DFTs of all pairs run
+// together and the last stage writes the picked, deconvolved samples X_n = s_n
+// conj(G_k), k = (n - nt/2) mod m, to memory.
 template <typename T>
 __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline1(StageArgs a) {
   const int NT = blockDim.x, tid = threadIdx.x;
@@ -745,8 +746,8 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline1(StageArgs a
   const int P0 = li * np, npi = min(np, I.npair - P0);
   const cx<T>* in = static_cast<const cx<T>*>(a.in[inst]);
   cx<T>* out = static_cast<cx<T>*>(a.out[inst]);
-  // (the depth scratch is the grid region when it is large enough; each pair's
-  // natural-order spectra go to dz)
+  // (the depth scratch lies in the grid region, the plan has seen to its size; each
+  // pair's natural-order spectra go to dz)
   px<T>* zs = buf;
   depth_first<T>(gz, zs, twz, npi, [&](int p, int h, int j, const cx<T>*, cx<T>* v, auto tag) {
     const int line = pair_line(I, P0 + p, h);

@@ -1967,10 +1967,13 @@ struct Runner {
     return mx;
   }
 
-  // The pipelined transverse kernels run for one instance; lengths of 128,
-  // 256 and 512 points with the plan's tile width take the compile-time
-  // instances (FP64 only these: its run-time-size pipelines, sized for the
-  // largest tile, would spill), other FP32 lengths the run-time-size ones.
+  // The pipelined transverse kernels run for one instance where neither the Fixed
+  // nor the general-length kernels do: before a bf16 grid, in small launches
+  // (short_pass), for lengths without a general plan (578) and for arrays of 4 GiB
+  // and more.  Lengths of 128, 256 and 512 points with the plan's tile width take
+  // the compile-time instances (FP64 only these: its run-time-size pipelines,
+  // sized for the largest tile, would spill), other FP32 lengths the run-time-size
+  // ones.
   hipError_t x1(const void* const* in, void* const* out, bool nz) {
     StageArgs a = base(IT_X1, nz, 0, in, out);
     const int len = nz ? h[0].nz : h[0].nt;
@@ -2036,7 +2039,10 @@ struct Runner {
         if constexpr (RS == 0) {
           const int L = h[0].n1, tb = h[0].tb;
           if (L == 128 && tb == pipe_tb<T>(7)) return go(k_tr_c2r_pipe<T, RS, 7>);
-          if (L == 256 && tb == pipe_tb<T>(8)) return go(k_tr_c2r_pipe<T, RS, 8>);
+          // (FP32 arrays of 256 points and this tile end below 4 GiB: the general kernels' range)
+          if constexpr (sizeof(T) == 8) {
+            if (L == 256 && tb == pipe_tb<T>(8)) return go(k_tr_c2r_pipe<T, RS, 8>);
+          }
           if (L == 512 && tb == pipe_tb<T>(9)) return go(k_tr_c2r_pipe<T, RS, 9>);
         }
         if constexpr (sizeof(T) == 4) return go(k_tr_c2r_pipe<T, RS>);

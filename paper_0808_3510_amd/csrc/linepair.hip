@@ -10,7 +10,8 @@
 // (k_line_nufft1_w): 174 us, and 40 against 31 for 128^3.  Where the chip is not filled
 // the shorter chains of k_line_nufft1_w win (64^3: 14 against 18.6 us; see takes).  In
 // FP64 (32 bytes a pair point, two waves per SIMD): 367 us against 412 for 256^3,
-// 57 against 79 for 128^3.
+// 57 against 79 for 128^3.  (No instance for m = 2048 or nz = m/2: R^T and A at 512^3 run
+// k_line_nufft1_c, nt = nz k_line_nufft1_w.)
 #include "general.h"
 #include "linepair.h"
 
