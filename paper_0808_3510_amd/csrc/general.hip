@@ -279,21 +279,17 @@ __global__ __launch_bounds__(kBlock, gtr_waves<T>()) void k_gtr_c2r(StageArgs a)
 // "pair" is one line there, its second half zero.
 
 // The roots of the middle stage for tw_powers in LDS: butterfly j takes the powers d of
-// root 8 j, d = 1, 2, 4, 8, 3, 12 in row 0 .. 5 as far as r1 asks for them (tw8_rows).
-__device__ __forceinline__ constexpr int tw8_row(int d) { return d <= 2 ? d - 1 : d == 4 ? 2 : d == 8 ? 3 : d == 3 ? 4 : 5; }
+// root 8 j, d = 1, 4, 2, 3, 8, 12 in row 0 .. 5 as far as r1 asks for them (tw8_rows).
+__device__ __forceinline__ constexpr int tw8_row(int d) { return d == 1 ? 0 : d == 4 ? 1 : d < 4 ? d : d / 4 + 2; }
 template <typename T>
 __device__ __forceinline__ void grid_roots(CFft& g, cx<T>* tw8, const cx<T>* tm) {
-  const int rows = tw8_rows(g.r1, (int)sizeof(cx<T>));
-  for (int e = threadIdx.x; e < rows * g.rl; e += (int)blockDim.x) {
-    const int row = fdiv(e, g.m_rl), j = e - row * g.rl;
-    const int d = row < 4 ? 1 << row : row == 4 ? 3 : 12;
-    tw8[e] = tm[8 * j * d];
+  for (int e = threadIdx.x; e < kTw8 * tw8_rows(g.r1, (int)sizeof(cx<T>)); e += (int)blockDim.x) {
+    const int row = e / kTw8, j = e % kTw8;
+    const int d = row == 0 ? 1 : row == 1 ? 4 : row < 4 ? row : 4 * (row - 2);
+    if (j < g.rl) tw8[e] = tm[8 * j * d];
   }
 }
 
-// Stages of the grid FFT (r0 = 8, r1 a power of two, rl one of 8, 10, 12,
-// 14, 16) over the np pairs of an item.  Pair p's points sit at p * rows, point i
-// in row d1 bs + d2 rlp + e (see GFft); NT threads.
 // (tw8: see grid_roots)
 template <typename T>
 __device__ __forceinline__ void grid_mid(CFft& g, px<T>* buf, const cx<T>* tw8, int np) {
@@ -310,7 +306,7 @@ __device__ __forceinline__ void grid_mid(CFft& g, px<T>* buf, const cx<T>* tw8, 
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = s[r * g.rlp];
         dft_px<T, R>(v);
-        twiddle_px<T, R>(v, [&](int d) { return tw8[tw8_row(d) * g.rl + j]; });
+        twiddle_px<T, R>(v, [&](int d) { return tw8[kTw8 * tw8_row(d) + j]; });
 #pragma unroll
         for (int r = 0; r < R; ++r) s[r * g.rlp] = v[r];
       } else {
@@ -322,7 +318,7 @@ __device__ __forceinline__ void grid_mid(CFft& g, px<T>* buf, const cx<T>* tw8, 
 #pragma unroll
           for (int r = 0; r < R; ++r) v[r] = c[2 * r * g.rlp];
           dft_reg<T, R>(v);
-          twiddle_reg<T, R>(v, [&](int d) { return tw8[tw8_row(d) * g.rl + j]; });
+          twiddle_reg<T, R>(v, [&](int d) { return tw8[kTw8 * tw8_row(d) + j]; });
 #pragma unroll
           for (int r = 0; r < R; ++r) c[2 * r * g.rlp] = v[r];
         }
@@ -553,7 +549,7 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a
   };
   int cur = -1;
   T snr[4] = {T(0), T(0), T(0), T(0)};
-  cx<T> w1[3] = {zero, zero, zero};  // first-stage roots 1, 2, 4 (FP64: 1)
+  cx<T> w1 = zero, w4 = zero;  // first-stage roots (FP64: w1)
   int item = blockIdx.x;
   if (item < a.total) fetch(item);
   for (; item < a.total; item += gridDim.x) {
@@ -577,11 +573,8 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a
         const int n = sample(I, j0, i);
         snr[i] = n >= 0 && n < I.nt ? sn[n] : T(0);
       }
-      w1[0] = tm[j0];
-      if constexpr (sizeof(T) == 4) {
-        w1[1] = tm[2 * j0];
-        w1[2] = tm[4 * j0];
-      }
+      w1 = tm[j0];
+      if constexpr (sizeof(T) == 4) w4 = tm[4 * j0];
       cur = inst;
       __syncthreads();
     }
@@ -597,7 +590,7 @@ __global__ __launch_bounds__(kBlock, gline_waves<T>()) void k_gline2(StageArgs a
       v[6] = in(2);
       v[7] = in(3);
       dft_px<T, 8>(v);
-      twiddle_px<T, 8>(v, [&](int d) { return w1[d / 2]; });
+      twiddle_px<T, 8>(v, [&](int d) { return d == 1 ? w1 : w4; });
       px<T>* s = buf + p0 * g.rows + j0 + fdiv(j0, g.m_rl) * (g.rlp - g.rl);
 #pragma unroll
       for (int r = 0; r < 8; ++r) s[r * g.bs] = v[r];

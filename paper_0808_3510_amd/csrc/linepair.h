@@ -69,17 +69,18 @@ __device__ __forceinline__ px<T> pmul(px<T> v, cx<T> w) {
 }
 
 // v[d] *= w^d, d = 1 .. R-1 (R a power of two up to 16).  FP32: root(d) reads w^d from
-// the table for d = 1, 2, 4 and 8, at R = 16 also 3 and 12, and the other powers are
-// products of two of those.  Powers of w alone, each square doubling the error of the
-// one before, took the error of a 1792-point transform from 8e-8 to 2.7e-7.  FP64 takes
-// the powers of w: their error, below 1e-15, is nothing beside the window's 1e-11.
-constexpr bool tw_read(int R, int d) { return (d & (d - 1)) == 0 || (R == 16 && (d == 3 || d == 12)); }
+// the table for d = 1 and 4, at R = 16 for 1 .. 4, 8 and 12, and the other powers are
+// products of those, one (R = 16) to three deep.  Powers of w alone, each square
+// doubling the error of the one before, took the error of a 1792-point transform from
+// 8e-8 to 2.7e-7.  FP64 takes the powers of w: their error, below 1e-15, is nothing
+// beside the window's 1e-11.
+constexpr bool tw_read(int R, int d) { return R == 16 ? d <= 4 || d % 4 == 0 : d == 1 || d == 4; }
 template <typename T, int R, typename Root>
 __device__ __forceinline__ void tw_powers(cx<T>* w, Root root) {
 #pragma unroll
   for (int d = 1; d < R; ++d) {
     if constexpr (sizeof(T) == 4)
-      w[d] = tw_read(R, d) ? root(d) : d < 4 ? cmul(w[2], w[1]) : cmul(w[d & ~3], w[d & 3]);
+      w[d] = tw_read(R, d) ? root(d) : d < 4 ? cmul(w[d - 1], w[1]) : cmul(w[d & ~3], w[d & 3]);
     else
       w[d] = d == 1 ? root(1) : (d & (d - 1)) == 0 ? cmul(w[d / 2], w[d / 2]) : cmul(w[d & (d - 1)], w[d & -d]);
   }

@@ -165,16 +165,17 @@ inline size_t lds_fused1(const Inst& I, size_t cs) {
 
 // general-length line kernels: np pairs of grid lines and of depth lines
 // (two complex values per point), the depth roots, the roots of the middle grid
-// stage (tw8_rows rows of rl)
+// stage
 // Grid lines of the paired line kernels lie in LDS as four planes by cell mod 4,
 // cell j at (j & 3) ps + (j >> 2).  The nodes of neighbouring lanes lie up to
 // m / nz cells apart, 4 at nt = 2 nz: in natural order the lanes of an LDS cycle
 // would meet in a quarter of its 16-byte banks.  With ps = 4 or 12 mod 16 cells 1,
 // 2 and 4 apart all spread over the 16.
 constexpr int plane_stride(int m) { return ((m / 4 + 3) & ~7) + 4; }
-constexpr int tw8_rows(int r1, int cs) { return r1 == 1 ? 0 : cs == 16 || r1 == 2 ? 1 : r1 == 4 ? 2 : r1 == 8 ? 3 : 6; }
+constexpr int kTw8 = 16;  // row length, the largest rl
+constexpr int tw8_rows(int r1, int cs) { return r1 == 1 ? 0 : cs == 16 || r1 <= 4 ? 1 : r1 == 8 ? 2 : 6; }
 inline size_t lds_gline(const Inst& I, int np, size_t cs) {
-  return ((size_t)np * (I.gm.rows + I.gz.rows) * 2 + I.nz + tw8_rows(I.gm.r1, (int)cs) * I.gm.rl) * cs;
+  return ((size_t)np * (I.gm.rows + I.gz.rows) * 2 + I.nz + kTw8 * tw8_rows(I.gm.r1, (int)cs)) * cs;
 }
 // general-length transverse passes: a tile and the roots
 inline size_t lds_gtile(const GFft& g, int tb, size_t cs) { return ((size_t)g.rows * tb + g.L) * cs; }
